@@ -50,11 +50,12 @@ class Sizes(ctypes.Structure):
 
 
 _lib = None
+_F32 = _I16 = None   # torch.float32, torch.int16 (PyTorch is imported with the library)
 
 
 def lib() -> ctypes.CDLL:
     """The loaded library.  Raises if it has not been built (no CPU or PyTorch fallback)."""
-    global _lib
+    global _lib, _F32, _I16
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -63,13 +64,35 @@ def lib() -> ctypes.CDLL:
         # PyTorch ships its own HIP runtime (same soname as the system one).  Import it first so
         # that this library binds to the runtime that owns PyTorch's device memory and streams;
         # two HIP runtimes in one process do not see each other's devices.
-        import torch  # noqa: F401
+        import torch
+
+        _F32, _I16 = torch.float32, torch.int16
 
         _lib = ctypes.CDLL(LIB_PATH)
         _lib.cpoconv_strerror.restype = ctypes.c_char_p
         for name in EXPORTS:
             getattr(_lib, name)  # fail loudly on a missing symbol
+        for name, types in _LAUNCHING.items():   # plain integers as pointers and sizes: no wrapper object per argument
+            getattr(_lib, name).argtypes = types
     return _lib
+
+
+_P, _I, _L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+_ENCODE, _ENCODE_BATCH = [_P, _P, _P, _P, _L, _P], [_P, _P, _I, _P, _P, _L, _P]
+_CONV, _CONV_BATCH = [_P, _P, _P, _P, _P, _L, _P], [_P, _P, _I, _P, _P, _P, _L, _P]
+_LAYER, _LAYER_BATCH = [_P, _P, _P, _P, _P, _P, _L, _P], [_P, _P, _I, _P, _P, _P, _P, _L, _P]
+_RELU = [_P, _P, _P, _I, _P, _P, _L, _P]
+# argument types of the calls that queue work
+_LAUNCHING = {
+    "cpo_encode": _ENCODE, "cps_encode": _ENCODE, "cpo_encode_batch": _ENCODE_BATCH, "cps_encode_batch": _ENCODE_BATCH,
+    "cpo_conv": _CONV, "cps_conv": _CONV, "cpo_conv_batch": _CONV_BATCH, "cps_conv_batch": _CONV_BATCH,
+    "cpo_encode_conv": _LAYER, "cps_encode_conv": _LAYER,
+    "cpo_encode_conv_batch": _LAYER_BATCH, "cps_encode_conv_batch": _LAYER_BATCH,
+    "cpo_encode_relu": _RELU, "cps_encode_relu": _RELU,
+    "im2col_conv": [_P, _P, _P, _P, _P, _I, _P], "im2col_conv_batch": [_P, _P, _I, _P, _P, _P, _I, _P],
+    "im2col_conv_relu": [_P, _P, _P, _I, _P, _P, _P, _I, _P],
+    "cpoconv_chain_forward": [_P, _P, _I, _I, _P, _P, _L, _P, _L, _P],
+}
 
 
 EXPORTS = (
@@ -132,6 +155,23 @@ def make_shape(shape) -> Shape:
     return Shape(*v)
 
 
+_SHAPE_ARGS: dict = {}
+
+
+def _shape_arg(shape):
+    """A reference to the Shape a call takes.  Tuples - what most programs pass, the same few again and
+    again - are converted once; the table of them is bounded."""
+    if type(shape) is tuple:
+        ref = _SHAPE_ARGS.get(shape)
+        if ref is None:
+            ref = ctypes.byref(make_shape(shape))
+            if len(_SHAPE_ARGS) >= 1024:
+                _SHAPE_ARGS.clear()
+            _SHAPE_ARGS[shape] = ref
+        return ref
+    return ctypes.byref(make_shape(shape))
+
+
 def cpoconv_sizes(shape) -> Sizes:
     sz = Sizes()
     sh = make_shape(shape)
@@ -170,30 +210,44 @@ def select_layer_algo(t_im2col: Sequence[float], t_cpo: Optional[Sequence[float]
 # device-side calls (torch tensors supply the memory)
 # ----------------------------------------------------------------------------------------
 
-def _stream_handle(stream) -> ctypes.c_void_p:
-    import torch
-
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+_raw_stream = None   # (device) -> handle of its current stream; (-> the current device)
 
 
-def _weights_ptr(weights, precision: int) -> ctypes.c_void_p:
+def _stream_handle(stream) -> int:
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+
+        # the handle itself where PyTorch offers it: current_stream() builds a stream object on every call
+        c = torch._C
+        if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice"):
+            torch.cuda.init()
+            _raw_stream = (c._cuda_getCurrentRawStream, c._cuda_getDevice)
+        else:
+            _raw_stream = (lambda device: torch.cuda.current_stream(device).cuda_stream, torch.cuda.current_device)
+    return _raw_stream[0](_raw_stream[1]())
+
+
+def _weights_ptr(weights, precision: int) -> int:
     """im2col weights: fp32 K x C x kh x kw for precision 0 and 1, the int16-typed bf16 kernel matrix
     of im2col_prepare_weights_bf16 for precision 2."""
-    import torch
-
-    return _dev_ptr(weights, torch.int16 if int(precision) == 2 else torch.float32)
+    return _dev_ptr(weights, _I16 if int(precision) == 2 else _F32)
 
 
-def _dev_ptr(t, dtype=None) -> ctypes.c_void_p:
+def _dev_ptr(t, dtype=None) -> Optional[int]:
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _bytes(t) -> int:
+    return t.numel() * t.element_size()
 
 
 class EncodedMap:
@@ -224,6 +278,16 @@ class EncodedMap:
                     ctypes.c_void_p(self.chan_off.data_ptr() + 4 * image * 3 * (self.shape.C + 1)),
                     ctypes.c_void_p(self.hdr.data_ptr() + 4 * image * 8), self.in_bits)
 
+    def _batch_ref(self):
+        """A reference to the struct of image 0 (the whole batch to the batched calls), kept while the
+        buffers stay where they are."""
+        at = (self.ptr.data_ptr(), self.da.data_ptr(), self.ind.data_ptr(), self.chan_off.data_ptr(), self.hdr.data_ptr(),
+              self.sizes, self.in_bits)
+        kept = self.__dict__.get("_kept")
+        if kept is None or kept[0] != at:
+            kept = self._kept = (at, ctypes.byref(self.c_struct()))
+        return kept[1]
+
     def view(self, shape) -> "EncodedMap":
         """The same buffers seen as the map of another layer shape (a chain's layers share one map;
         the side band's stride between images follows the layer's channel count)."""
@@ -247,13 +311,8 @@ class EncodedMap:
 
 
 def _encode(fn_name: str, act, shape, m: EncodedMap, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(getattr(lib(), fn_name)(_dev_ptr(act, torch.float32), ctypes.byref(sh), ctypes.byref(cm),
-                                   _dev_ptr(scratch), ctypes.c_int64(scratch.numel() * scratch.element_size()),
-                                   _stream_handle(stream)))
+    _check(getattr(lib(), fn_name)(_dev_ptr(act, _F32), _shape_arg(shape), m._batch_ref(), _dev_ptr(scratch),
+                                   _bytes(scratch), _stream_handle(stream)))
 
 
 def cpo_encode(act, shape, m: EncodedMap, scratch, stream=None) -> None:
@@ -266,31 +325,18 @@ def cps_encode(act, shape, m: EncodedMap, scratch, stream=None) -> None:
 
 def cpo_encode_static_scratch(act, shape, m: EncodedMap, stream=None) -> None:
     """cpo_encode without a scratch buffer from the caller (the library's own device array)."""
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(lib().cpo_encode_static_scratch(_dev_ptr(act, torch.float32), ctypes.byref(sh), ctypes.byref(cm),
-                                           _stream_handle(stream)))
+    _check(lib().cpo_encode_static_scratch(ctypes.c_void_p(_dev_ptr(act, _F32)), _shape_arg(shape), m._batch_ref(),
+                                           ctypes.c_void_p(_stream_handle(stream))))
 
 
 def cpoconv_prepare_weights(weights, shape, wt, stream=None) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    _check(lib().cpoconv_prepare_weights(_dev_ptr(weights, torch.float32), ctypes.byref(sh),
-                                         _dev_ptr(wt, torch.float32), _stream_handle(stream)))
+    _check(lib().cpoconv_prepare_weights(ctypes.c_void_p(_dev_ptr(weights, _F32)), _shape_arg(shape),
+                                         ctypes.c_void_p(_dev_ptr(wt, _F32)), ctypes.c_void_p(_stream_handle(stream))))
 
 
 def _conv(fn_name: str, m: EncodedMap, shape, wt, out, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(getattr(lib(), fn_name)(ctypes.byref(cm), ctypes.byref(sh), _dev_ptr(wt, torch.float32),
-                                   _dev_ptr(out, torch.float32), _dev_ptr(scratch),
-                                   ctypes.c_int64(scratch.numel() * scratch.element_size()),
-                                   _stream_handle(stream)))
+    _check(getattr(lib(), fn_name)(m._batch_ref(), _shape_arg(shape), _dev_ptr(wt, _F32), _dev_ptr(out, _F32),
+                                   _dev_ptr(scratch), _bytes(scratch), _stream_handle(stream)))
 
 
 def cpo_conv(m: EncodedMap, shape, wt, out, scratch, stream=None) -> None:
@@ -302,27 +348,20 @@ def cps_conv(m: EncodedMap, shape, wt, out, scratch, stream=None) -> None:
 
 
 def im2col_conv(act, shape, weights, lowered, out, precision: int = 0, stream=None) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    _check(lib().im2col_conv(_dev_ptr(act, torch.float32), ctypes.byref(sh), _weights_ptr(weights, precision),
-                             _dev_ptr(lowered), _dev_ptr(out, torch.float32), int(precision),
-                             _stream_handle(stream)))
+    _check(lib().im2col_conv(_dev_ptr(act, _F32), _shape_arg(shape), _weights_ptr(weights, precision),
+                             _dev_ptr(lowered), _dev_ptr(out, _F32), int(precision), _stream_handle(stream)))
 
 
 def im2col_prepare_weights_bf16(weights, shape, wb, stream=None) -> None:
     """wb: int16 device tensor of cpoconv_sizes(shape).wb_len elements (bf16 bit patterns)."""
-    import torch
-
-    sh = make_shape(shape)
-    _check(lib().im2col_prepare_weights_bf16(_dev_ptr(weights, torch.float32), ctypes.byref(sh),
-                                             _dev_ptr(wb, torch.int16), _stream_handle(stream)))
+    _check(lib().im2col_prepare_weights_bf16(ctypes.c_void_p(_dev_ptr(weights, _F32)), _shape_arg(shape),
+                                             ctypes.c_void_p(_dev_ptr(wb, _I16)), ctypes.c_void_p(_stream_handle(stream))))
 
 
 def cpoconv_map_header_to_host(m: EncodedMap, stream=None, image=0):
     cm = m.c_struct(image)
     hdr = (ctypes.c_int32 * 8)()
-    rc = lib().cpoconv_map_header_to_host(ctypes.byref(cm), hdr, _stream_handle(stream))
+    rc = lib().cpoconv_map_header_to_host(ctypes.byref(cm), hdr, ctypes.c_void_p(_stream_handle(stream)))
     if rc == ERR_MAP:      # the header is filled in all the same: the error carries it
         err = CpoconvError(rc, cpoconv_strerror(rc))
         err.hdr = [int(v) for v in hdr]
@@ -357,8 +396,8 @@ class LayerBuffers:
 
 def cpoconv_scratch_init(scratch, stream=None) -> None:
     """Zero-fills a scratch buffer: required once before its first use (see include/cpoconv.h)."""
-    _check(lib().cpoconv_scratch_init(_dev_ptr(scratch), ctypes.c_int64(scratch.numel() * scratch.element_size()),
-                                      _stream_handle(stream)))
+    _check(lib().cpoconv_scratch_init(ctypes.c_void_p(_dev_ptr(scratch)), ctypes.c_int64(_bytes(scratch)),
+                                      ctypes.c_void_p(_stream_handle(stream))))
 
 
 def cpoconv_batch_sizes(shape, n_images: int) -> Sizes:
@@ -368,13 +407,8 @@ def cpoconv_batch_sizes(shape, n_images: int) -> Sizes:
 
 
 def _encode_batch(fn_name: str, act, shape, m: EncodedMap, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(getattr(lib(), fn_name)(_dev_ptr(act, torch.float32), ctypes.byref(sh), int(m.n_images), ctypes.byref(cm),
-                                   _dev_ptr(scratch), ctypes.c_int64(scratch.numel() * scratch.element_size()),
-                                   _stream_handle(stream)))
+    _check(getattr(lib(), fn_name)(_dev_ptr(act, _F32), _shape_arg(shape), m.n_images, m._batch_ref(),
+                                   _dev_ptr(scratch), _bytes(scratch), _stream_handle(stream)))
 
 
 def cpo_encode_batch(act, shape, m: EncodedMap, scratch, stream=None) -> None:
@@ -386,14 +420,8 @@ def cps_encode_batch(act, shape, m: EncodedMap, scratch, stream=None) -> None:
 
 
 def _conv_batch(fn_name: str, m: EncodedMap, shape, wt, out, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(getattr(lib(), fn_name)(ctypes.byref(cm), ctypes.byref(sh), int(m.n_images), _dev_ptr(wt, torch.float32),
-                                   _dev_ptr(out, torch.float32), _dev_ptr(scratch),
-                                   ctypes.c_int64(scratch.numel() * scratch.element_size()),
-                                   _stream_handle(stream)))
+    _check(getattr(lib(), fn_name)(m._batch_ref(), _shape_arg(shape), m.n_images, _dev_ptr(wt, _F32),
+                                   _dev_ptr(out, _F32), _dev_ptr(scratch), _bytes(scratch), _stream_handle(stream)))
 
 
 def cpo_conv_batch(m: EncodedMap, shape, wt, out, scratch, stream=None) -> None:
@@ -405,47 +433,33 @@ def cps_conv_batch(m: EncodedMap, shape, wt, out, scratch, stream=None) -> None:
 
 
 def im2col_conv_batch(act, shape, n_images: int, weights, lowered, out, precision: int = 0, stream=None) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    _check(lib().im2col_conv_batch(_dev_ptr(act, torch.float32), ctypes.byref(sh), int(n_images),
-                                   _weights_ptr(weights, precision), _dev_ptr(lowered), _dev_ptr(out, torch.float32),
+    _check(lib().im2col_conv_batch(_dev_ptr(act, _F32), _shape_arg(shape), int(n_images),
+                                   _weights_ptr(weights, precision), _dev_ptr(lowered), _dev_ptr(out, _F32),
                                    int(precision), _stream_handle(stream)))
 
 
 # ---- encoding + convolution of a layer in one call ---------------------------------------------
 
 def _encode_conv(fn_name: str, act, shape, m: EncodedMap, wt, out, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    args = [_dev_ptr(act, torch.float32), ctypes.byref(sh)]
-    if fn_name.endswith("_batch"):
-        args.append(int(m.n_images))
-    args += [ctypes.byref(cm), _dev_ptr(wt, torch.float32), _dev_ptr(out, torch.float32), _dev_ptr(scratch),
-             ctypes.c_int64(scratch.numel() * scratch.element_size()), _stream_handle(stream)]
-    _check(getattr(lib(), fn_name)(*args))
+    # (the batched entry point with one image is the single-image call)
+    _check(getattr(lib(), fn_name)(_dev_ptr(act, _F32), _shape_arg(shape), m.n_images, m._batch_ref(),
+                                   _dev_ptr(wt, _F32), _dev_ptr(out, _F32), _dev_ptr(scratch), _bytes(scratch),
+                                   _stream_handle(stream)))
 
 
 def cpo_encode_conv(act, shape, m: EncodedMap, wt, out, scratch, stream=None) -> None:
-    _encode_conv("cpo_encode_conv" if m.n_images == 1 else "cpo_encode_conv_batch", act, shape, m, wt, out, scratch, stream)
+    _encode_conv("cpo_encode_conv_batch", act, shape, m, wt, out, scratch, stream)
 
 
 def cps_encode_conv(act, shape, m: EncodedMap, wt, out, scratch, stream=None) -> None:
-    _encode_conv("cps_encode_conv" if m.n_images == 1 else "cps_encode_conv_batch", act, shape, m, wt, out, scratch, stream)
+    _encode_conv("cps_encode_conv_batch", act, shape, m, wt, out, scratch, stream)
 
 
 # ---- a layer's input produced on the way in (bias and ReLU of the layer before it) --------------
 
 def _encode_relu(fn_name: str, pre, bias, shape, m: EncodedMap, scratch, stream) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    cm = m.c_struct()
-    _check(getattr(lib(), fn_name)(_dev_ptr(pre, torch.float32), _dev_ptr(bias, torch.float32), ctypes.byref(sh),
-                                   int(m.n_images), ctypes.byref(cm), _dev_ptr(scratch),
-                                   ctypes.c_int64(scratch.numel() * scratch.element_size()), _stream_handle(stream)))
+    _check(getattr(lib(), fn_name)(_dev_ptr(pre, _F32), _dev_ptr(bias, _F32), _shape_arg(shape), m.n_images,
+                                   m._batch_ref(), _dev_ptr(scratch), _bytes(scratch), _stream_handle(stream)))
 
 
 def cpo_encode_relu(pre, bias, shape, m: EncodedMap, scratch, stream=None) -> None:
@@ -457,12 +471,9 @@ def cps_encode_relu(pre, bias, shape, m: EncodedMap, scratch, stream=None) -> No
 
 
 def im2col_conv_relu(pre, bias, shape, n_images: int, weights, lowered, out, precision: int = 0, stream=None) -> None:
-    import torch
-
-    sh = make_shape(shape)
-    _check(lib().im2col_conv_relu(_dev_ptr(pre, torch.float32), _dev_ptr(bias, torch.float32), ctypes.byref(sh),
+    _check(lib().im2col_conv_relu(_dev_ptr(pre, _F32), _dev_ptr(bias, _F32), _shape_arg(shape),
                                   int(n_images), _weights_ptr(weights, precision), _dev_ptr(lowered),
-                                  _dev_ptr(out, torch.float32), int(precision), _stream_handle(stream)))
+                                  _dev_ptr(out, _F32), int(precision), _stream_handle(stream)))
 
 
 # ---- chained layers ------------------------------------------------------------------------------
@@ -502,7 +513,7 @@ class Chain:
             self.table[i].shape = sh
             self.table[i].precision = self.precision
             self.table[i].relu_in = self.relu_in[i]
-            self.table[i].bias_in = _dev_ptr(self.biases[i], torch.float32).value
+            self.table[i].bias_in = _dev_ptr(self.biases[i], torch.float32)
             self.table[i].out = self.outs[i].data_ptr()
         sz = cpoconv_chain_sizes(self.table, self.n_images)
         self.sizes = sz
@@ -526,7 +537,7 @@ class Chain:
                     self.prepared_bf16[i] = wb
                 self.table[i].weights = self.prepared_bf16[i].data_ptr()
             elif m == ALGO_IM2COL:
-                self.table[i].weights = _dev_ptr(self.weights[i], torch.float32).value
+                self.table[i].weights = _dev_ptr(self.weights[i], torch.float32)
             else:
                 if self.prepared[i] is None:
                     wt = torch.empty(cpoconv_sizes(sh).wt_len, dtype=torch.float32, device=self.device)
@@ -537,12 +548,8 @@ class Chain:
     def forward(self, act, stream=None, first=0, count=None) -> None:
         """Runs every layer; layer i's output (before bias / ReLU) lands in outs[i].  With first /
         count only layers first .. first+count-1 run, `act` being the input of layer `first`."""
-        import torch
-
         count = len(self.shapes) - first if count is None else count
-        cm = self.map.c_struct()
-        sub = ctypes.cast(ctypes.byref(self.table, first * ctypes.sizeof(ChainLayer)), ctypes.POINTER(ChainLayer))
-        _check(lib().cpoconv_chain_forward(_dev_ptr(act, torch.float32), sub, int(count), self.n_images,
-                                           ctypes.byref(cm), _dev_ptr(self.scratch),
-                                           ctypes.c_int64(self.scratch.numel()), _dev_ptr(self.lowered),
-                                           ctypes.c_int64(self.lowered.numel()), _stream_handle(stream)))
+        sub = ctypes.byref(self.table, first * ctypes.sizeof(ChainLayer))
+        _check(lib().cpoconv_chain_forward(_dev_ptr(act, _F32), sub, int(count), self.n_images, self.map._batch_ref(),
+                                           _dev_ptr(self.scratch), self.scratch.numel(), _dev_ptr(self.lowered),
+                                           self.lowered.numel(), _stream_handle(stream)))
