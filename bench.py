@@ -2,7 +2,7 @@
 """Benchmark of the CPO / CPS convolution hot path on one MI355X.
 
 A step is one pass of the whole path over one layer: CPO encode + SpMV conv, CPS encode +
-SpMV conv, im2col lowering + MFMA GEMM (fp32), and the per-layer selection.  Inputs are
+convolution of the encoded map, the dense comparator (fp32), and the per-layer selection.  Inputs are
 resident in HBM before the timed region.  Prints ONE JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 2] [--all-layers]
@@ -134,7 +134,7 @@ def algorithmic_figures(spec, lens, act_np):
         "cpo_conv_bytes": 8 * nnz + 4 * ptr + wbytes + 4 * out_elems,
         "cps_conv_bytes": 4 * nnz + 4 * lens["in_cps"] + 4 * ptr + wbytes + 4 * out_elems,
         "sparse_flops": sparse_flops(spec, act_np),
-        "im2col_f32_bytes": 4 * C * H * W + 2 * 4 * S + wbytes + 4 * out_elems,
+        "im2col_f32_bytes": 4 * C * H * W + wbytes + 4 * out_elems,   # lowered in LDS, not in memory
         "im2col_bf16_bytes": 4 * C * H * W + 2 * 2 * S + wbytes + 4 * out_elems,
         "dense_flops": float(spec.dense_flops),
         "s_im2col": S,
@@ -215,29 +215,24 @@ def kernel_roofline(stage, kernel, us, fig, spec, lens):
     C, H, W, K, kh, kw, s, p = spec.shape_tuple[:8]
     if stage.endswith("_layer"):     # kernels of the one-call stages belong to its encode or convolution half
         stage = stage[:3] + ("_encode" if kernel.startswith("encode") else "_conv")
-    out_bytes = 4 * K * spec.Oh * spec.Ow
     hbm = lambda b: {"bound": "hbm", "achieved": b / t / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": b / t / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes": b}
     if kernel == "encode_count":      # layers of more than 256 channels: a first launch publishes the lengths
         return hbm(4 * C * H * W)
     if kernel == "encode":
         return hbm(fig[stage + "_bytes"])
-    if kernel == "conv_prologue":
-        b = 4 * lens["ptr"] + 4 * C * 2 * (spec.Ow + 1)
-        if stage == "cps_conv":
-            b += 4 * lens["in_cps"] + 4 * lens["nnz"]
-        return hbm(b)
-    if kernel.startswith("spmv_conv_"):   # runs, strip, tile or lds: whichever the layer was given
+    if kernel == "column_table":     # 16-byte entry per channel, padded column and band of 64 padded rows
+        in_len = lens["in_cps"] if stage == "cps_conv" else lens["nnz"]
+        return hbm(4 * lens["ptr"] + 4 * in_len + 16 * C * (W + 2 * (p if spec.pad_w is None else spec.pad_w)) * ((H + 2 * p + 63) // 64))
+    if kernel == "spmv_conv":
         r = stage_roofline(stage, us, fig)
         r["algorithmic_flops"] = fig["sparse_flops"]
         r["algorithmic_bytes"] = fig[stage + "_bytes"]
         return r
-    if kernel == "reduce_transpose":
-        return hbm(2 * out_bytes)
-    if kernel.startswith("im2col_lower"):
-        return hbm(4 * C * H * W + (4 if kernel.endswith("f32") else 2) * fig["s_im2col"])
-    if kernel.startswith("gemm"):
-        peak = FP32_MFMA_PEAK_TFLOPS if kernel == "gemm_f32" else BF16_MFMA_PEAK_TFLOPS
+    if kernel == "im2col_lower_bf16":
+        return hbm(4 * C * H * W + 2 * fig["s_im2col"])
+    if kernel in ("im2col_conv_f32", "gemm_bf16"):
+        peak = FP32_MFMA_PEAK_TFLOPS if kernel == "im2col_conv_f32" else BF16_MFMA_PEAK_TFLOPS
         tf = fig["dense_flops"] / t / 1e12
         return {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,
                 "algorithmic_flops": fig["dense_flops"]}

@@ -81,10 +81,8 @@ int check_shape(const cpoconv_shape *s)
 // A padded column j lies in partitions p with p*stride <= j <= p*stride + kw - 1, 0 <= p < Ow
 // (Section 3.1: Ow partitions of width kw separated by the stride).  Its overlap type is the
 // number of such partitions minus one; the first of them indexes the column (Section 3.2).
-int build_geometry(const cpoconv_shape *s, Geometry *g)
+static void make_geometry(const cpoconv_shape *s, Geometry *g)
 {
-    const int rc = check_shape(s);
-    if (rc != CPOCONV_OK) return rc;
     memset(g, 0, sizeof(*g));
     g->C = s->C; g->H = s->H; g->W = s->W; g->K = s->K;
     g->channel_last = s->layout == CPOCONV_LAYOUT_HWC ? 1 : 0;
@@ -135,6 +133,14 @@ int build_geometry(const cpoconv_shape *s, Geometry *g)
         for (int i = 0; i < g->n_types; ++i)
             if (g->type_id[i] == top) { g->top = top; g->top_slot = i; }
     }
+}
+
+int build_geometry(const cpoconv_shape *s, Geometry *g)
+{
+    static thread_local ShapeCache<cpoconv_shape, Geometry, 64> cache;
+    const int rc = check_shape(s);
+    if (rc != CPOCONV_OK) return rc;
+    *g = cache.get(*s, [s](Geometry &made) { make_geometry(s, &made); });
     return CPOCONV_OK;
 }
 
@@ -147,29 +153,12 @@ int64_t max_ptr_len(const Geometry &g)
     return per_channel * g.C;
 }
 
-// Scratch layout: the encoder's look-back words (epochs, per-band stream lengths) | the convolution's
-// table of resolved ptr offsets | one int16 per NZE for the indices cps_conv rebuilds | partial
-// sums of the convolution | the column table of the column-run convolution.
-// (each region holds g.N images back to back, with the per-image strides below)
-int64_t indices_stride(const Geometry &g) { return static_cast<int64_t>(g.C) * g.H * g.W; }                 // entries
-int64_t mtab_stride(const Geometry &g) { return static_cast<int64_t>(g.C) * std::max(g.n_types, 1) * (g.Ow + 1); }   // ints
-int64_t columns_stride(const Geometry &g) { return static_cast<int64_t>(g.C) * g.Iw; }                       // entries
-
-// encoder look-back words: the fixed region every scratch buffer starts with (its place and size do
-// not depend on the call, so calls of any shape and batch size may share a buffer), then the words
-// of a call that takes two launches
+// Scratch layout: the encoder's look-back words - the fixed region every scratch buffer starts with (its
+// place and size do not depend on the call, so calls of any shape and batch size may share a buffer),
+// then the words of a call that takes two launches -, then the column table of the convolution.
 int64_t scratch_counts_bytes(const Geometry &g) { return encode_fixed_bytes() + encode_call_flags_bytes(g); }
-int64_t scratch_indices_bytes(const Geometry &g) { return (2 * indices_stride(g) * g.N + 255) / 256 * 256; }   // int16 each
-int64_t scratch_mtab_bytes(const Geometry &g) { return (4 * mtab_stride(g) * g.N + 255) / 256 * 256; }
 
-int64_t scratch_columns_offset(const Geometry &g)
-{
-    const int64_t partial = std::max(std::max(tile_kernel_partial_bytes(g), strip_kernel_partial_bytes(g)),
-                                     std::max(runs_kernel_partial_bytes(g), lds_kernel_partial_bytes(g)));
-    return scratch_counts_bytes(g) + scratch_mtab_bytes(g) + scratch_indices_bytes(g) + (partial + 255) / 256 * 256;
-}
-
-int64_t scratch_bytes_for(const Geometry &g) { return scratch_columns_offset(g) + runs_kernel_columns_bytes(g); }
+int64_t scratch_bytes_for(const Geometry &g) { return scratch_columns_offset(g) + column_table_bytes(g); }
 
 }  // namespace cpoconv
 
@@ -347,17 +336,10 @@ static int encode_conv_common(const float *act, const cpoconv_shape *shape, int 
     if (map->ptr_cap < max_ptr_len(g) || map->da_cap < chw || map->in_cap < chw) return CPOCONV_ERR_SMALL;
     if (scratch_bytes < scratch_bytes_for(g)) return CPOCONV_ERR_SMALL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // the encoder also leaves the table of resolved ptr offsets: the convolution needs no prologue
-    // of its own; for a CPS map it also leaves there the plain index of every NZE (16 bits each: what
-    // Algorithm 4 rebuilds from the packed IN stream, which the map itself holds as after cps_encode)
-    // (not where the column-run convolution follows: the column table is all it reads, and where the
-    // encoder does not leave it, it is rebuilt from the packed stream itself)
-    const bool table = sparse_conv_uses_prologue(g);
-    const bool columns = table && encode_writes_columns(g);
-    const bool indices = algo == CPOCONV_ALGO_CPS && g.top_slot >= 0 && !runs_kernel_preferred(g);
-    const int erc = launch_encode(act, prod, g, *map, algo, scratch, st, table, indices);
+    // the encoder leaves the column table: the convolution starts without a pass over the streams
+    const int erc = launch_encode(act, prod, g, *map, algo, scratch, st, true);
     if (erc != CPOCONV_OK) return erc;
-    return launch_sparse_conv(*map, g, algo, wt, out, scratch, st, table, indices, columns);
+    return launch_sparse_conv(*map, g, algo, wt, out, scratch, st, true);
 }
 
 int cpo_encode_conv(const float *act, const cpoconv_shape *shape, const cpoconv_map *map, const float *wt,

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <type_traits>
 
@@ -43,33 +44,30 @@ __device__ __forceinline__ int64_t map_index(const Geometry &g, int c, int hr, i
                           : (static_cast<int64_t>(c) * g.H + hr) * g.W + jr;
 }
 
-// Element strides between consecutive images of a batched launch (image 0 is at the base pointers).
-struct BatchStrides {
-    int64_t ptr, da, in;   // streams and side band: the per-image capacities of the map
-    int64_t indices;       // what the convolution reads as IN: the stream itself or the rebuilt CPS indices (entries)
-    int64_t mtab, partial, out;
-    int64_t columns;       // entries of the column table per image (column-run kernel)
-    int32_t map_in16;      // the map's IN stream holds int16 entries
-    int32_t indices16;     // so does what the convolution reads as IN (the rebuilt CPS indices always do)
-    const int32_t *hdr;    // the map's header (8 ints per image)
-    int32_t algo;          // the algorithm the call expects the map to hold
+// An entry of the column table, [image][channel][padded column][band of 64 padded rows]: where the
+// column's NZEs of these rows start in DA and which of the rows hold one.  Every padded column has
+// its entries; those of a column outside the streams (padding, or under no kernel position) are empty.
+struct ColumnEntry {
+    int32_t begin;             // absolute offset in DA
+    int32_t count;             // NZEs (= set bits)
+    uint32_t rows_lo, rows_hi; // bit r: row 64 * band + r holds an NZE
 };
 
-// What the column-run kernel knows of one padded column of one channel: where the column's run of
-// NZEs starts in DA and which padded rows hold one (maps of at most 64 padded rows).
-struct ColumnEntry {
-    int32_t begin;             // absolute offset of the run in DA
-    int32_t count;             // its length (= set bits)
-    uint32_t rows_lo, rows_hi; // bit r: padded row r holds an NZE
-};
+// Does padded column j belong to the streams: part of the unpadded map and under some partition?
+__device__ __forceinline__ bool encoded_column(const Geometry &g, int j)
+{
+    if (j < g.pad_w || j >= g.pad_w + g.W) return false;
+    const int first = j < g.kw ? 0 : (j - g.kw + g.stride) / g.stride;   // ceil((j - kw + 1) / stride)
+    return first <= min(j / g.stride, g.Ow - 1);
+}
 
 // A map the convolution must not read: its encoder gave up (hdr[7] equals the header's stamp), or it holds the other
 // algorithm's streams (hdr[3]).  Every kernel on the convolution side leaves its outputs alone then.
-__device__ __forceinline__ bool map_unusable(const BatchStrides &bs, int image)
+__device__ __forceinline__ bool map_unusable(const int32_t *hdr, int image, int algo)
 {
-    const int32_t *h = bs.hdr + static_cast<int64_t>(image) * 8;
+    const int32_t *h = hdr + static_cast<int64_t>(image) * 8;
     const int failed_in = h[7];   // stamp of the call in which an encoder unit gave up; hdr[6] >> 8: stamp of the header
-    return (failed_in != 0 && failed_in == (h[6] >> 8)) || h[3] != bs.algo;
+    return (failed_in != 0 && failed_in == (h[6] >> 8)) || h[3] != algo;
 }
 
 // IN entries: int32, or int16 in a compact map (same values).  The stream pointer is typed int32
@@ -109,6 +107,38 @@ __device__ __forceinline__ float produced(float v, const Producer &prod, float b
     return v;
 }
 
+// What a call works out on the host from a layer's shape alone is kept for the next call with that
+// shape: per thread, a fixed number of entries (a program has few layers, a slot is overwritten when two
+// fall on it).
+template <typename Key, typename Value, int kSlots>
+class ShapeCache {
+public:
+    // The value of `key`, made by make(value) if the slot does not hold it; valid until the next call.
+    template <typename Make> const Value &get(const Key &key, Make make)
+    {
+        const int32_t *words = reinterpret_cast<const int32_t *>(&key);
+        uint32_t hash = 2166136261u;
+        for (size_t i = 0; i < sizeof(Key) / sizeof(int32_t); ++i) hash = (hash ^ static_cast<uint32_t>(words[i])) * 16777619u;
+        Slot &slot = slots_[(hash ^ hash >> 15) % kSlots];
+        if (!slot.used || memcmp(&slot.key, &key, sizeof(Key)) != 0) {
+            slot.used = false;
+            make(slot.value);
+            slot.key = key;
+            slot.used = true;
+        }
+        return slot.value;
+    }
+
+private:
+    static_assert(sizeof(Key) % sizeof(int32_t) == 0 && std::is_trivially_copyable<Key>::value, "a key is compared by its words");
+    struct Slot {
+        bool used = false;
+        Key key;
+        Value value;
+    };
+    Slot slots_[kSlots];
+};
+
 int check_shape(const cpoconv_shape *s);           // CPOCONV_OK or CPOCONV_ERR_SHAPE
 int build_geometry(const cpoconv_shape *s, Geometry *g);
 int64_t max_ptr_len(const Geometry &g);
@@ -141,66 +171,25 @@ private:
 
 // launchers (defined next to their kernels)
 int launch_encode(const float *act, const Producer &prod, const Geometry &g, const cpoconv_map &map, int algo,
-                  void *scratch, hipStream_t stream, bool write_table = false, bool write_indices = false);
-bool encode_uses_channel_kernel(const Geometry &g); // the workgroup-per-channel encoder takes the layer
-bool encode_writes_columns(const Geometry &g);      // with write_table: does the encoder also leave the column table?
+                  void *scratch, hipStream_t stream, bool write_columns = false);
 int64_t encode_fixed_bytes();                        // look-back words every scratch buffer starts with
 int64_t encode_call_flags_bytes(const Geometry &g);  // look-back words of a call that takes two launches
 int launch_prepare_weights(const float *w, const Geometry &g, float *wt, hipStream_t stream);
 int launch_zero_fill(void *buffer, int64_t bytes, hipStream_t stream);
-int launch_sparse_conv(const cpoconv_map &map, const Geometry &g, int algo, const float *wt,
-                       float *out, void *scratch, hipStream_t stream, bool table_ready = false,
-                       bool indices_ready = false, bool columns_ready = false);
-bool sparse_conv_uses_prologue(const Geometry &g);
-int64_t lds_kernel_partial_bytes(const Geometry &g);   // general kernel (spmv_conv.hip)
-// register-tile SpMV kernel (spmv_conv_tile.hip)
-bool tile_kernel_supports(const Geometry &g);
-int64_t tile_kernel_partial_bytes(const Geometry &g);
-int launch_sparse_conv_tile(const cpoconv_map &map, const int32_t *indices, const int32_t *mtab, const Geometry &g, const float *wt,
-                            float *out, float *partial, BatchStrides bs, hipStream_t stream);
-// strip SpMV kernel (spmv_conv_strip.hip)
-bool strip_kernel_supports(const Geometry &g);
-bool strip_kernel_preferred(const Geometry &g);
-int64_t strip_kernel_partial_bytes(const Geometry &g);
-int launch_sparse_conv_strip(const cpoconv_map &map, const int32_t *indices, const int32_t *mtab, const Geometry &g,
-                             const float *wt, float *out, float *partial, BatchStrides bs, hipStream_t stream);
-// column-run SpMV kernel (spmv_conv_runs.hip)
-bool runs_kernel_supports(const Geometry &g);
-bool runs_kernel_preferred(const Geometry &g);
-int64_t runs_kernel_partial_bytes(const Geometry &g);
-int64_t runs_kernel_columns_bytes(const Geometry &g);
-int launch_column_table(const cpoconv_map &map, const int32_t *mtab, ColumnEntry *columns, const Geometry &g, BatchStrides bs,
-                        bool cps, hipStream_t stream);
-int launch_sparse_conv_runs(const cpoconv_map &map, const ColumnEntry *columns, const Geometry &g, const float *wt, float *out,
-                            float *partial, BatchStrides bs, hipStream_t stream);
-// byte offsets of the regions of the caller's scratch buffer
+// convolution over an encoded map (column_table.hip); columns_ready: the encoder of the same call left
+// the column table in the scratch buffer
+int launch_sparse_conv(const cpoconv_map &map, const Geometry &g, int algo, const float *wt, float *out, void *scratch,
+                       hipStream_t stream, bool columns_ready = false);
+int64_t column_table_bytes(const Geometry &g);
+// 64-row bands of a padded column
+__host__ __device__ inline int column_bands(const Geometry &g) { return (g.Ih + kLanes - 1) / kLanes; }
+// byte offsets inside the caller's scratch buffer: the encoder's look-back words, then the column table
 int64_t scratch_counts_bytes(const Geometry &g);
-int64_t scratch_indices_bytes(const Geometry &g);
-int64_t scratch_mtab_bytes(const Geometry &g);
-int64_t scratch_columns_offset(const Geometry &g);   // the column table comes last
-// per-image strides inside those regions, in 4-byte elements
-int64_t indices_stride(const Geometry &g);
-int64_t mtab_stride(const Geometry &g);
-int64_t columns_stride(const Geometry &g);           // in entries
-// out[k][y][x] = sum over channel slices of partial[slice][y][x][k] (spmv_conv.hip)
-int launch_reduce_transpose(const Geometry &g, const float *partial, int slices, int Ypad, int Xpad, float *out,
-                            const BatchStrides &bs, hipStream_t stream);   // per image: partial advances by slices*Ypad*Xpad*Kpad, out by K*Oh*Ow
-
-// Sum over the channel slices of one output element: four interleaved running sums, then
-// pairwise.  Every kernel that adds slices uses this order, so they agree bit for bit.
-__device__ inline float sum_slices(const float *src, int64_t slice_stride, int slices)
-{
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    int sl = 0;
-    for (; sl + 3 < slices; sl += 4) {
-        s0 += src[sl * slice_stride];
-        s1 += src[(sl + 1) * slice_stride];
-        s2 += src[(sl + 2) * slice_stride];
-        s3 += src[(sl + 3) * slice_stride];
-    }
-    for (; sl < slices; ++sl) s0 += src[sl * slice_stride];
-    return (s0 + s1) + (s2 + s3);
-}
+inline int64_t scratch_columns_offset(const Geometry &g) { return scratch_counts_bytes(g); }
+// products on the matrix cores (conv_mfma.hip): over the column table of an encoded map, over a dense map
+int launch_conv_columns(const cpoconv_map &map, const ColumnEntry *columns, const Geometry &g, int algo, const float *wt, float *out,
+                        hipStream_t stream);
+int launch_conv_dense_f32(const float *act, const Producer &prod, const Geometry &g, const float *w, float *out, hipStream_t stream);
 int64_t im2col_scratch_bytes(const Geometry &g);
 int64_t im2col_weights_bf16_len(const Geometry &g);
 int launch_prepare_weights_bf16(const float *w, const Geometry &g, uint16_t *wb, hipStream_t stream);

@@ -87,18 +87,6 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
     return v;
 }
 
-__device__ __forceinline__ int wave_inclusive_max(int v)
-{
-    constexpr int kLow = static_cast<int>(0x80000000u);   // identity of max
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x111, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x112, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x114, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x118, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x142, 0xa, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(kLow, v, 0x143, 0xc, 0xf, false));
-    return v;
-}
-
 __device__ __forceinline__ int wave_sum(int v)
 {
 #pragma unroll
@@ -203,9 +191,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
                                                             const int cps, const int tile_floats,
                                                             unsigned long long *__restrict__ ctrl,
                                                             unsigned long long *__restrict__ flags_all, const int units_stride,
-                                                            const cpoconv_map maps, int32_t *__restrict__ mtab_all,
-                                                            const int64_t mtab_stride, int16_t *__restrict__ full_all,
-                                                            const int64_t full_stride)
+                                                            const cpoconv_map maps, ColumnEntry *__restrict__ columns_all)
 {
     extern __shared__ float lds[];   // per wavefront: tile_floats (band columns x (Ih | 1), column-major), then 64 ints
 
@@ -231,8 +217,6 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
     map.in = index_advance(maps.in, image * maps.in_cap, in16);
     map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
     map.hdr += image * 8;
-    // for a CPS convolution launched by the same call: the plain index of every NZE, laid out like DA
-    int16_t *__restrict__ full = full_all != nullptr ? full_all + image * full_stride : nullptr;
 
     // ---- load: lane = (row phase rp, column col); CW columns side by side, 64 / CW rows per pass ------
     int cw_log2 = 0;
@@ -441,8 +425,27 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
         map.hdr[5] = g.Ow;
     }
 
-    // ---- ptr of the band's types and, for a convolution of the same call, the table of absolute DA
-    // offsets after every partition (what Algorithm 2 gets by forward-filling ptr) ------------------------
+    // ---- for a convolution of the same call: the column table (band 0 also writes the columns outside the streams) --
+    if (columns_all != nullptr) {
+        const int row_bands = column_bands(g);
+        ColumnEntry *table = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw * row_bands;
+        if (lane < nb) {
+            int at = da_off + da_before + excl;
+#pragma unroll
+            for (int w = 0; w < kMaskWords; ++w) {
+                if (w >= row_bands) continue;
+                const int n = __popcll(m[w]);
+                table[g.col_j[vi] * row_bands + w] =
+                    ColumnEntry{at, n, static_cast<uint32_t>(m[w]), static_cast<uint32_t>(m[w] >> 32)};
+                at += n;
+            }
+        }
+        if (b == 0)
+            for (int i = lane; i < g.Iw * row_bands; i += kLanes)
+                if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0, 0u, 0u};
+    }
+
+    // ---- ptr of the band's types ------------------------------------------------------------------------
     if (!live && b == 0 && lane == 0) map.ptr[ptr_off] = CPOCONV_NPC;
     {
         const int my_p0 = static_cast<int>(g.col_p0[vb + min(lane, nb - 1)]);
@@ -457,13 +460,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             const int local = (ce == ve ? nnz_u : bcast(excl, ce - vb)) - local_before;
             const int t_before = my_slot == kWholeTypes ? 0 : type_before;
             const int t_total = my_slot == kWholeTypes ? local : type_total;
-            const int type_start = da_off + da_before + local_before - t_before;   // first NZE of the type in DA
             const int p_begin = has_first ? 0 : static_cast<int>(g.col_p0[cb]);
             const int p_end = has_last ? g.Ow : static_cast<int>(g.col_p0[ce]);
-            int32_t *row = mtab_all != nullptr
-                               ? mtab_all + image * mtab_stride + (static_cast<int64_t>(c) * g.n_types + i) * (g.Ow + 1)
-                               : nullptr;
-            if (row != nullptr && has_first && lane == 0) row[0] = type_start;
             const bool nop3 = g.nop3 && g.type_id[i] == 0;
             const bool entries = live && t_total > 0 && !nop3;        // the segment has its Ow cumulative entries
             if (live && has_first && lane == 0) {
@@ -480,8 +478,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             }
             // partitions p_begin .. p_end-1, 64 at a time: cumulative count of the type after the last
             // column first seen in the partition, -1 where no column of the type is first seen
-            int carry = t_before;                                      // count after the partitions before p_begin
-            for (int p0 = p_begin; p0 < p_end; p0 += kLanes) {
+            for (int p0 = p_begin; entries && p0 < p_end; p0 += kLanes) {
                 tblw[lane] = -1;
                 wave_lds_fence();
                 const int at = vb + lane;
@@ -489,11 +486,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
                     (at + 1 == ce || next_p0 != my_p0))
                     tblw[my_p0 - p0] = t_before + incl - local_before;
                 wave_lds_fence();
-                const int e = tblw[lane], p = p0 + lane;
-                if (entries && p < p_end) map.ptr[seg + 1 + p] = e;
-                const int filled = max(wave_inclusive_max(e), carry);
-                if (row != nullptr && p < p_end) row[1 + p] = type_start + filled;
-                carry = bcast(filled, kLanes - 1);
+                if (p0 + lane < p_end) map.ptr[seg + 1 + p0 + lane] = tblw[lane];
                 wave_lds_fence();
             }
             seg += live ? segment_length(g, i, t_total) : 0;
@@ -526,7 +519,6 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             const int rank = __popcll(mask & below);
             const int index = what + h * g.kw;
             if (nz) map.da[at_da + rank] = tile[src * IhP + h];
-            if (nz && full != nullptr) full[at_da + rank] = static_cast<int16_t>(index);
             if (packed) {
                 // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
                 const int pattern = static_cast<int>((mask >> (hl & ~3)) & 0xFull);
@@ -569,10 +561,7 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
                                                          const Producer prod, const int cps, const int kChunk,
                                                          unsigned long long *__restrict__ ctrl,
                                                          unsigned long long *__restrict__ flags_all, const int units_stride,
-                                                         const cpoconv_map maps, int32_t *__restrict__ mtab_all,
-                                                         const int64_t mtab_stride, int16_t *__restrict__ full_all,
-                                                         const int64_t full_stride, ColumnEntry *__restrict__ columns_all,
-                                                         const int64_t columns_stride)
+                                                         const cpoconv_map maps, ColumnEntry *__restrict__ columns_all)
 {
     // image blockIdx.y of the launch: its map is image 0's advanced by the per-image capacities
     const int image = blockIdx.y;
@@ -588,7 +577,6 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     map.in = index_advance(maps.in, image * maps.in_cap, in16);
     map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
     map.hdr += image * 8;
-    int16_t *__restrict__ full = full_all != nullptr ? full_all + image * full_stride : nullptr;   // as in the band kernel
 
     extern __shared__ float tile[];                    // kChunk x Wt, Wt odd: conflict-free column reads
     __shared__ uint16_t cnt_q[kMaxChunks][kMaxCols];   // NZEs per (row chunk, column), then their
@@ -644,7 +632,8 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     // order) and leaves its part of every column's row bitmap in LDS; one thread per column then
     // puts the eight parts together ------------------------------------------------------------
     const int rows_per_wave = kChunk / kWaves;   // 8
-    unsigned long long rows_first = 0;           // column tid: the bitmap of its first 64 padded rows
+    const int row_bands = column_bands(g);       // (= chunks: a chunk has 64 rows)
+    ColumnEntry *table = columns_all != nullptr ? columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw * row_bands : nullptr;
     for (int q = 0; q < nchunks; ++q) {
         if (q > 0) {
             __syncthreads();   // every thread is done with the previous chunk
@@ -670,7 +659,12 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
             cnt_q[q][tid] = static_cast<uint16_t>(__popcll(mask));
             ecnt_q[q][tid] = static_cast<uint16_t>((tid >= top_begin && tid < top_end) ? set4_entries(mask)
                                                                                       : __popcll(mask));
-            if (q == 0) rows_first = mask;
+            if (table != nullptr) {   // the entry's rows now, its place in DA when that is known
+                ColumnEntry *e = table + g.col_j[tid] * row_bands + q;
+                e->count = __popcll(mask);
+                e->rows_lo = static_cast<uint32_t>(mask);
+                e->rows_hi = static_cast<uint32_t>(mask >> 32);
+            }
         }
     }
 
@@ -776,37 +770,12 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
             }
     }
 
-    // ---- for a convolution that follows in the same call: the table of absolute DA offsets after
-    // every partition (what Algorithm 2 gets by forward-filling ptr), per present type ----------
-    if (mtab_all != nullptr) {
-        for (int i = 0; i < g.n_types; ++i) {
-            int32_t *row = mtab_all + image * mtab_stride + (static_cast<int64_t>(c) * g.n_types + i) * (g.Ow + 1);
-            const int cb = g.type_begin[i], ce = g.type_begin[i + 1];
-            const int base = type_base[i], at = da_off + base;
-            const int p_first = cb < ce ? col_p0[cb] : g.Ow;        // partitions before it hold nothing of the type
-            for (int k = tid; k <= p_first; k += kThreads) row[k] = at;
-            for (int vi = cb + tid; vi < ce; vi += kThreads) {
-                const int p_end = vi + 1 < ce ? col_p0[vi + 1] : g.Ow;
-                const int upto = at + col_excl[vi + 1] - base;
-                for (int pp = col_p0[vi]; pp < p_end; ++pp) row[1 + pp] = upto;
-            }
-        }
-    }
-
-    // ---- and, for the column-run convolution (maps of at most 64 padded rows: one chunk): where every
-    // padded column's run starts in DA and which padded rows it holds; padding columns hold nothing
-    if (columns_all != nullptr) {
-        ColumnEntry *row = columns_all + image * columns_stride + static_cast<int64_t>(c) * g.Iw;
-        if (tid < g.n_cols) {
-            ColumnEntry e;
-            e.begin = da_off + col_excl[tid];
-            e.count = col_excl[tid + 1] - col_excl[tid];
-            e.rows_lo = static_cast<uint32_t>(rows_first);
-            e.rows_hi = static_cast<uint32_t>(rows_first >> 32);
-            row[g.col_j[tid]] = e;
-        }
-        for (int j = tid; j < g.Iw; j += kThreads)
-            if (j < g.pad_w || j >= g.pad_w + g.W) row[j] = ColumnEntry{0, 0, 0u, 0u};
+    // ---- for a convolution of the same call: the column table --------------------------------------
+    if (table != nullptr) {
+        if (tid < g.n_cols)
+            for (int q = 0; q < nchunks; ++q) table[g.col_j[tid] * row_bands + q].begin = da_off + col_excl[tid] + cnt_q[q][tid];
+        for (int i = tid; i < g.Iw * row_bands; i += kThreads)
+            if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0, 0u, 0u};
     }
 
     // ---- ptr of this channel -------------------------------------------------------------
@@ -864,7 +833,6 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
             const int in_at = in_off + ecol_excl[vi] + ecnt_q[q][vi];
             const int index = static_cast<int>(col_wh[vi]) + (q * kChunk + lane) * g.kw;
             if (nz) map.da[da_at + rank] = v;
-            if (nz && full != nullptr) full[da_at + rank] = static_cast<int16_t>(index);
             if (vi >= top_begin && vi < top_end) {
                 // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
                 const int pattern = static_cast<int>((mask >> (lane & ~3)) & 0xFull);
@@ -899,10 +867,7 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
                                                                    unsigned long long *__restrict__ ctrl,
                                                                    unsigned long long *__restrict__ flags_all,
                                                                    const int units_stride, const cpoconv_map maps,
-                                                                   int32_t *__restrict__ mtab_all, const int64_t mtab_stride,
-                                                                   int16_t *__restrict__ full_all, const int64_t full_stride,
-                                                                   ColumnEntry *__restrict__ columns_all,
-                                                                   const int64_t columns_stride)
+                                                                   ColumnEntry *__restrict__ columns_all)
 {
     extern __shared__ float tile[];                              // Ih x Wt, Wt odd: conflict-free column reads
     __shared__ unsigned long long parts[kLanes];                 // a column's row bitmap: piece w (64 / NW bits) from wavefront w
@@ -922,7 +887,6 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
     map.in = index_advance(maps.in, image * maps.in_cap, in16);
     map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
     map.hdr += image * 8;
-    int16_t *__restrict__ full = full_all != nullptr ? full_all + image * full_stride : nullptr;
 
     const int Wt = g.W | 1;
     const int top_begin = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot] : kMaxCols + 1;
@@ -1124,29 +1088,12 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
         }
     }
 
-    // ---- for a convolution of the same call: the table of absolute DA offsets after every partition
-    // (overlap type i by wavefront i mod 8) and the column table of the column-run kernel -----------
-    if (mtab_all != nullptr) {
-#pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types || (i & (NW - 1)) != wave) continue;
-            int32_t *row = mtab_all + image * mtab_stride + (static_cast<int64_t>(c) * g.n_types + i) * (g.Ow + 1);
-            const int cb = g.type_begin[i], ce = g.type_begin[i + 1];
-            const int at = da_off + type_base[i];
-            const int p_first = cb < ce ? static_cast<int>(g.col_p0[cb]) : g.Ow;
-            for (int k = lane; k <= p_first; k += kLanes) row[k] = at;
-            if (lane >= cb && lane < ce) {
-                const int p_end = lane + 1 < ce ? next_p0 : g.Ow;
-                const int upto = da_off + incl;
-                for (int pp = my_p0; pp < p_end; ++pp) row[1 + pp] = upto;
-            }
-        }
-    }
+    // ---- for a convolution of the same call: the column table ----------------------------------------
     if (columns_all != nullptr && wave == NW - 1) {
-        ColumnEntry *row = columns_all + image * columns_stride + static_cast<int64_t>(c) * g.Iw;
+        ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
         if (col_ok)
             row[g.col_j[lane]] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
-        if (lane < g.Iw && (lane < g.pad_w || lane >= g.pad_w + g.W)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
+        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
     }
 
     // ---- ptr: overlap type i by wavefront i mod 8 ----------------------------------------------------
@@ -1199,8 +1146,6 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
             const bool nz = is_nze(item_v[n]);
             const int rank = item_n[n] & 127, erank = ((item_n[n] >> 7) & 127) - 1, entry = item_n[n] >> 16;
             if (nz) map.da[da_at + rank] = item_v[n];
-            if (nz && full != nullptr)
-                full[da_at + rank] = static_cast<int16_t>(static_cast<int>(g.col_what[vi]) + lane * g.kw);
             if (erank >= 0) store_index(map.in, in_at + erank, entry, in16);
         }
     }
@@ -1226,9 +1171,7 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
                                                                const Producer prod, const int cps,
                                                                unsigned long long *__restrict__ ctrl,
                                                                unsigned long long *__restrict__ flags_all, const int units_stride,
-                                                               const cpoconv_map maps, int32_t *__restrict__ mtab_all,
-                                                               const int64_t mtab_stride, int16_t *__restrict__ full_all,
-                                                               const int64_t full_stride)
+                                                               const cpoconv_map maps, ColumnEntry *__restrict__ columns_all)
 {
     extern __shared__ float tiles[];                   // per wavefront: H x Wt floats, then 64 ints of ptr staging
     __shared__ int32_t grp[kWaves][3];                 // the group's lengths: ptr, DA, IN per channel
@@ -1251,7 +1194,6 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
     map.in = index_advance(maps.in, image * maps.in_cap, in16);
     map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
     map.hdr += image * 8;
-    int16_t *__restrict__ full = full_all != nullptr ? full_all + image * full_stride : nullptr;
 
     const int Wt = g.W | 1;
     const int per_wave = g.H * Wt + kLanes;            // floats of LDS per wavefront
@@ -1393,22 +1335,12 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
             }
     }
 
-    // ---- the table of absolute DA offsets after every partition, for a convolution of the same call ----
-    if (mtab_all != nullptr) {
-#pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types) continue;
-            int32_t *row = mtab_all + image * mtab_stride + (static_cast<int64_t>(c) * g.n_types + i) * (g.Ow + 1);
-            const int cb = g.type_begin[i], ce = g.type_begin[i + 1];
-            const int at = da_off + type_base[i];
-            const int p_first = cb < ce ? static_cast<int>(g.col_p0[cb]) : g.Ow;
-            for (int k = lane; k <= p_first; k += kLanes) row[k] = at;
-            if (lane >= cb && lane < ce) {
-                const int p_end = lane + 1 < ce ? next_p0 : g.Ow;
-                const int upto = da_off + incl;
-                for (int pp = my_p0; pp < p_end; ++pp) row[1 + pp] = upto;
-            }
-        }
+    // ---- for a convolution of the same call: the column table ----------------------------------------
+    if (columns_all != nullptr) {
+        ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
+        if (col_ok)
+            row[g.col_j[lane]] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
+        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
     }
 
     // ---- ptr ----------------------------------------------------------------------------------------
@@ -1470,7 +1402,6 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
         const int rank = __popcll(mask & below);
         const int index = what + h * g.kw;
         if (nz) map.da[at_da + rank] = v;
-        if (nz && full != nullptr) full[at_da + rank] = static_cast<int16_t>(index);
         const bool packed = on && vi >= top_begin && vi < top_end;
         // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
         const int pattern = static_cast<int>((mask >> (h & ~3)) & 0xFull);
@@ -1565,7 +1496,7 @@ bool build_bands(const Geometry &g, int cpb, EncodePlan *plan)
 // channel-images in the launch, narrower bands, so that about 768 bands exist (three per compute
 // unit) while a band keeps eight columns or more; one launch needs at most kUnitsPerImage bands per
 // image.  `single_pass`: the look-back words of the call fit the fixed region.
-EncodePlan plan_encode(const Geometry &g, bool *single_pass)
+EncodePlan make_encode_plan(const Geometry &g, bool *single_pass)
 {
     const int IhP = g.Ih | 1;
     int group = 1;   // columns sharing a first partition stay in one band: leave room for the largest group
@@ -1595,6 +1526,22 @@ EncodePlan plan_encode(const Geometry &g, bool *single_pass)
     for (int cpb = std::min(cap, std::max(8, (g.n_cols + bands_wanted - 1) / bands_wanted)); cpb < cap; ++cpb)
         if (build_bands(g, cpb, &plan) && static_cast<int64_t>(g.C) * plan.B <= kUnitsPerImage) return plan;
     return widest;
+}
+
+EncodePlan plan_encode(const Geometry &g, bool *single_pass)
+{
+    struct Key {
+        int32_t C, H, W, kh, kw, stride, pad_h, pad_w, N;
+    };
+    struct Made {
+        EncodePlan plan;
+        bool single_pass;
+    };
+    static thread_local ShapeCache<Key, Made, 16> cache;
+    const Made &made = cache.get(Key{g.C, g.H, g.W, g.kh, g.kw, g.stride, g.pad_h, g.pad_w, g.N},
+                                 [&](Made &m) { m.plan = make_encode_plan(g, &m.single_pass); });
+    *single_pass = made.single_pass;
+    return made.plan;
 }
 
 int64_t fixed_scratch_bytes() { return (8 * kFixedWords + 255) / 256 * 256; }
@@ -1627,7 +1574,7 @@ int64_t encode_call_flags_bytes(const Geometry &g)
 int64_t encode_fixed_bytes() { return fixed_scratch_bytes(); }
 
 static int launch_encode_bands(const float *act, const Producer &prod, const Geometry &g, const cpoconv_map &map, int cps,
-                               void *scratch, hipStream_t stream, int32_t *mtab, int64_t mstride, int16_t *full, int64_t fstride)
+                               void *scratch, hipStream_t stream, ColumnEntry *columns)
 {
     bool single_pass;
     const EncodePlan plan = plan_encode(g, &single_pass);
@@ -1644,19 +1591,18 @@ static int launch_encode_bands(const float *act, const Producer &prod, const Geo
     if (single_pass) {
         KernelTimer timer("encode", stream);
         hipLaunchKernelGGL(encode_kernel<kSinglePass>, grid, block, lds, stream, g, plan, act, prod, cps, tile_floats,
-                           ctrl, ctrl + kCtrlWords, kUnitsPerImage, map, mtab, mstride, full, fstride);
+                           ctrl, ctrl + kCtrlWords, kUnitsPerImage, map, columns);
     } else {
         unsigned long long *call_flags = reinterpret_cast<unsigned long long *>(static_cast<char *>(scratch) + fixed_scratch_bytes());
         {
             KernelTimer timer("encode_count", stream);
             hipLaunchKernelGGL(encode_kernel<kPublishOnly>, grid, block, lds, stream, g, plan, act, prod, cps,
-                               tile_floats, ctrl, call_flags, units, map, static_cast<int32_t *>(nullptr), mstride,
-                               static_cast<int16_t *>(nullptr), fstride);
+                               tile_floats, ctrl, call_flags, units, map, static_cast<ColumnEntry *>(nullptr));
         }
         CPOCONV_HIP_TRY(hipGetLastError());
         KernelTimer timer("encode", stream);
         hipLaunchKernelGGL(encode_kernel<kPublished>, grid, block, lds, stream, g, plan, act, prod, cps, tile_floats,
-                           ctrl, call_flags, units, map, mtab, mstride, full, fstride);
+                           ctrl, call_flags, units, map, columns);
     }
     CPOCONV_HIP_TRY(hipGetLastError());
     return CPOCONV_OK;
@@ -1667,41 +1613,19 @@ static int launch_encode_bands(const float *act, const Producer &prod, const Geo
 // queue for a compute unit.
 static bool use_small(const Geometry &g)
 {
-    // Where the column-run convolution can follow (fewer than four images, a shape it is instantiated for) the
-    // workgroup-per-channel encoder takes the small maps too: it leaves the column table, and the
-    // layer gains more from that kernel than the encoder loses (256 x 14 x 14: 28.8 -> 24.5 us for
-    // the one-call layer, 512 x 7 x 7: 28.4 -> 26.6, the encoder alone 9.7 -> 12.0).
-    if (g.N < 4 && runs_kernel_supports(g)) return false;
     const size_t small_tile = static_cast<size_t>(g.H) * (g.W | 1) * sizeof(float);
     const bool worth = g.Ih * g.Iw <= kSmallAlways || static_cast<int64_t>(g.N) * g.C >= kSmallFromChannels;
     return g.Ih <= kLanes && g.Iw <= kLanes && small_tile <= kSmallTileBytes && worth;
 }
 
-// The workgroup-per-channel kernel is the one that leaves the column table (for layers the
-// column-run convolution takes); after the other two the convolution rebuilds it from the streams.
-bool encode_uses_channel_kernel(const Geometry &g) { return !use_bands(g) && !use_small(g); }
-bool encode_writes_columns(const Geometry &g) { return runs_kernel_preferred(g) && encode_uses_channel_kernel(g); }
-
 int launch_encode(const float *act, const Producer &prod, const Geometry &g, const cpoconv_map &map, int algo,
-                  void *scratch, hipStream_t stream, bool write_table, bool write_indices)
+                  void *scratch, hipStream_t stream, bool write_columns)
 {
-    // the plain per-NZE indices, for a CPS convolution launched by the same call (same place and
-    // layout as the convolution's own reconstruction would leave them)
-    int16_t *full = write_indices ? reinterpret_cast<int16_t *>(static_cast<char *>(scratch) + scratch_counts_bytes(g) +
-                                                                scratch_mtab_bytes(g))
-                                  : nullptr;
-    const int64_t fstride = indices_stride(g);
-    // the table of resolved ptr offsets, for a convolution launched by the same call
-    int32_t *mtab = write_table ? reinterpret_cast<int32_t *>(static_cast<char *>(scratch) + scratch_counts_bytes(g)) : nullptr;
-    const int64_t mstride = mtab_stride(g);
     const int cps = algo == CPOCONV_ALGO_CPS ? 1 : 0;
-    if (use_bands(g)) return launch_encode_bands(act, prod, g, map, cps, scratch, stream, mtab, mstride, full, fstride);
-    // the column table of the column-run convolution, where that kernel takes the layer
-    ColumnEntry *columns = (write_table && encode_writes_columns(g))
-                               ? reinterpret_cast<ColumnEntry *>(static_cast<char *>(scratch) + scratch_columns_offset(g))
-                               : nullptr;
-    const int64_t cstride = columns_stride(g);
-    if (columns != nullptr) mtab = nullptr;   // the column-run convolution reads the column table only
+    // the column table, for a convolution launched by the same call
+    ColumnEntry *columns = write_columns ? reinterpret_cast<ColumnEntry *>(static_cast<char *>(scratch) + scratch_columns_offset(g))
+                                         : nullptr;
+    if (use_bands(g)) return launch_encode_bands(act, prod, g, map, cps, scratch, stream, columns);
 
     unsigned long long *ctrl = static_cast<unsigned long long *>(scratch);
     const bool single = channels_single_pass(g);
@@ -1720,17 +1644,17 @@ int launch_encode(const float *act, const Producer &prod, const Geometry &g, con
         if (single) {
             KernelTimer timer("encode", stream);
             hipLaunchKernelGGL(encode_small_kernel<kSinglePass>, grid, dim3(kThreads), lds_small, stream, g, act, prod, cps, ctrl,
-                               flags, units_stride, map, mtab, mstride, full, fstride);
+                               flags, units_stride, map, columns);
         } else {
             {
                 KernelTimer timer("encode_count", stream);
                 hipLaunchKernelGGL(encode_small_kernel<kPublishOnly>, grid, dim3(kThreads), lds_small, stream, g, act, prod, cps,
-                                   ctrl, flags, units_stride, map, static_cast<int32_t *>(nullptr), mstride, static_cast<int16_t *>(nullptr), fstride);
+                                   ctrl, flags, units_stride, map, static_cast<ColumnEntry *>(nullptr));
             }
             CPOCONV_HIP_TRY(hipGetLastError());
             KernelTimer timer("encode", stream);
             hipLaunchKernelGGL(encode_small_kernel<kPublished>, grid, dim3(kThreads), lds_small, stream, g, act, prod, cps, ctrl,
-                               flags, units_stride, map, mtab, mstride, full, fstride);
+                               flags, units_stride, map, columns);
         }
         CPOCONV_HIP_TRY(hipGetLastError());
         return CPOCONV_OK;
@@ -1747,22 +1671,18 @@ int launch_encode(const float *act, const Producer &prod, const Geometry &g, con
                        flags, units_stride, map, __VA_ARGS__)
         if (single) {
             KernelTimer timer("encode", stream);
-            if (narrow) CPOCONV_ENCODE64(kSinglePass, 4, mtab, mstride, full, fstride, columns, cstride);
-            else CPOCONV_ENCODE64(kSinglePass, 8, mtab, mstride, full, fstride, columns, cstride);
+            if (narrow) CPOCONV_ENCODE64(kSinglePass, 4, columns);
+            else CPOCONV_ENCODE64(kSinglePass, 8, columns);
         } else {
             {
                 KernelTimer timer("encode_count", stream);
-                if (narrow)
-                    CPOCONV_ENCODE64(kPublishOnly, 4, static_cast<int32_t *>(nullptr), mstride, static_cast<int16_t *>(nullptr), fstride,
-                                     static_cast<ColumnEntry *>(nullptr), cstride);
-                else
-                    CPOCONV_ENCODE64(kPublishOnly, 8, static_cast<int32_t *>(nullptr), mstride, static_cast<int16_t *>(nullptr), fstride,
-                                     static_cast<ColumnEntry *>(nullptr), cstride);
+                if (narrow) CPOCONV_ENCODE64(kPublishOnly, 4, static_cast<ColumnEntry *>(nullptr));
+                else CPOCONV_ENCODE64(kPublishOnly, 8, static_cast<ColumnEntry *>(nullptr));
             }
             CPOCONV_HIP_TRY(hipGetLastError());
             KernelTimer timer("encode", stream);
-            if (narrow) CPOCONV_ENCODE64(kPublished, 4, mtab, mstride, full, fstride, columns, cstride);
-            else CPOCONV_ENCODE64(kPublished, 8, mtab, mstride, full, fstride, columns, cstride);
+            if (narrow) CPOCONV_ENCODE64(kPublished, 4, columns);
+            else CPOCONV_ENCODE64(kPublished, 8, columns);
         }
 #undef CPOCONV_ENCODE64
         CPOCONV_HIP_TRY(hipGetLastError());
@@ -1771,18 +1691,17 @@ int launch_encode(const float *act, const Producer &prod, const Geometry &g, con
     if (single) {
         KernelTimer timer("encode", stream);
         hipLaunchKernelGGL(encode_channel_kernel<kSinglePass>, dim3(g.C, g.N), dim3(kThreads), lds, stream, g, act, prod, cps, chunk,
-                           ctrl, flags, units_stride, map, mtab, mstride, full, fstride, columns, cstride);
+                           ctrl, flags, units_stride, map, columns);
     } else {
         {
             KernelTimer timer("encode_count", stream);
             hipLaunchKernelGGL(encode_channel_kernel<kPublishOnly>, dim3(g.C, g.N), dim3(kThreads), lds, stream, g, act, prod, cps,
-                               chunk, ctrl, flags, units_stride, map, static_cast<int32_t *>(nullptr), mstride, static_cast<int16_t *>(nullptr), fstride,
-                               static_cast<ColumnEntry *>(nullptr), cstride);
+                               chunk, ctrl, flags, units_stride, map, static_cast<ColumnEntry *>(nullptr));
         }
         CPOCONV_HIP_TRY(hipGetLastError());
         KernelTimer timer("encode", stream);
         hipLaunchKernelGGL(encode_channel_kernel<kPublished>, dim3(g.C, g.N), dim3(kThreads), lds, stream, g, act, prod, cps, chunk,
-                           ctrl, flags, units_stride, map, mtab, mstride, full, fstride, columns, cstride);
+                           ctrl, flags, units_stride, map, columns);
     }
     CPOCONV_HIP_TRY(hipGetLastError());
     return CPOCONV_OK;

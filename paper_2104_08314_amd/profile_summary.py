@@ -18,10 +18,8 @@ from collections import defaultdict
 
 csv.field_size_limit(1 << 30)
 
-OURS = ("encode_kernel", "encode_small_kernel", "encode_channel_kernel", "encode_channel64_kernel", "column_table_kernel", "conv_prologue_kernel", "conv_prologue_wave_kernel",
-        "zero_fill_kernel", "spmv_conv_tile_kernel", "spmv_conv_strip_kernel", "spmv_conv_runs_kernel",
-        "spmv_conv_lds_kernel", "reduce_transpose_kernel", "im2col_lower_kernel", "im2col_lower_direct_kernel",
-        "gemm_f32_kernel", "gemm_bf16_kernel", "splitk_reduce_kernel", "prepare_weights_kernel", "prepare_weights_bf16_kernel")
+OURS = ("encode_kernel", "encode_small_kernel", "encode_channel_kernel", "encode_channel64_kernel", "column_table_kernel",
+        "zero_fill_kernel", "conv_f32_kernel", "im2col_lower_kernel", "im2col_lower_direct_kernel", "gemm_bf16_kernel", "splitk_reduce_kernel", "prepare_weights_kernel", "prepare_weights_bf16_kernel")
 
 
 def _find(directory, suffix):
@@ -36,18 +34,17 @@ def short_name(name):
     encoders keep their names (encode: column bands; encode_channel / encode_channel64: a workgroup
     per channel, the latter for maps up to 64 x 64 padded cells; encode_small: a wavefront per
     channel - the library's timing aid calls all of them encode), a
-    publish-only instantiation gets _count appended; the lowering kernels are named for their
-    output type, the direct one (small launches) with _direct appended."""
+    publish-only instantiation gets _count appended; the fp32 convolution is named for its reader
+    (spmv_conv: encoded map, im2col_conv_f32: dense map), as by the library's timing aid."""
     name = name.replace("(anonymous namespace)::", "")
     base = re.split(r"[<(]", name, 1)[0].replace("void ", "").split("::")[-1].strip()
     short = base[:-len("_kernel")] if base.endswith("_kernel") else base
     if short in ("encode", "encode_channel", "encode_channel64", "encode_small"):
         m = re.search(r"_kernel<\(?(?:[\w:]+\))?\s*(\w+)", name)
         return short + "_count" if (m and m.group(1) == "1") else short
-    if short in ("im2col_lower", "im2col_lower_direct"):
-        m = re.search(r"_kernel<\s*(\w+)", name)
-        kind = "bf16" if (m and m.group(1) in ("true", "1")) else "f32"
-        return "im2col_lower_" + kind + ("_direct" if short.endswith("direct") else "")
+    if short == "conv_f32":
+        m = re.search(r"_kernel<\s*\w+,\s*\w+,\s*(\w+)", name)
+        return "im2col_conv_f32" if (m and m.group(1) in ("true", "1")) else "spmv_conv"
     return short
 
 
