@@ -135,7 +135,7 @@ def algorithmic_figures(spec, lens, act_np):
         "cps_conv_bytes": 4 * nnz + 4 * lens["in_cps"] + 4 * ptr + wbytes + 4 * out_elems,
         "sparse_flops": sparse_flops(spec, act_np),
         "im2col_f32_bytes": 4 * C * H * W + wbytes + 4 * out_elems,   # lowered in LDS, not in memory
-        "im2col_bf16_bytes": 4 * C * H * W + 2 * 2 * S + wbytes + 4 * out_elems,
+        "im2col_bf16_bytes": 4 * C * H * W + wbytes // 2 + 4 * out_elems,
         "dense_flops": float(spec.dense_flops),
         "s_im2col": S,
         "cr_cpo": S / float(ptr + 2 * nnz),
@@ -229,9 +229,7 @@ def kernel_roofline(stage, kernel, us, fig, spec, lens):
         r["algorithmic_flops"] = fig["sparse_flops"]
         r["algorithmic_bytes"] = fig[stage + "_bytes"]
         return r
-    if kernel == "im2col_lower_bf16":
-        return hbm(4 * C * H * W + 2 * fig["s_im2col"])
-    if kernel in ("im2col_conv_f32", "gemm_bf16"):
+    if kernel in ("im2col_conv_f32", "im2col_conv_bf16"):
         peak = FP32_MFMA_PEAK_TFLOPS if kernel == "im2col_conv_f32" else BF16_MFMA_PEAK_TFLOPS
         tf = fig["dense_flops"] / t / 1e12
         return {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,

@@ -121,9 +121,8 @@ typedef struct {
     int64_t chan_off_len;  /* 3*(C+1)                                                      */
     int64_t wt_len;        /* prepared weights: C*kh*kw*round_up(K,64) floats              */
     int64_t out_len;       /* K*Oh*Ow                                                      */
-    int64_t lowered_bytes; /* im2col scratch of the bf16 calls: lowered matrix (rows padded */
-                           /* to 4 columns), split-K partial sums of the product, the bf16 */
-                           /* kernel matrix of a precision-1 call                          */
+    int64_t lowered_bytes; /* im2col scratch: 4*C*kh*kw*Oh*Ow, at least what a reordered   */
+                           /* bf16 kernel matrix takes                                     */
     int64_t scratch_bytes; /* scratch for encode and conv calls (prepare once with          */
                            /* cpoconv_scratch_init)                                         */
     int64_t wb_len;        /* bf16 kernel matrix of im2col_prepare_weights_bf16, in 16-bit  */
@@ -221,14 +220,13 @@ int cps_encode_conv(const float *act, const cpoconv_shape *shape, const cpoconv_
  * The comparator of Section 3.1: im2col lowering (lowered matrix C*kh*kw x Oh*Ow, row
  * (c*kh + l)*kw + w, column y*Ow + x, holds the padded input at (c, y*stride + l,
  * x*stride + w)) followed by a dense matrix product with the K x C*kh*kw kernel matrix on
- * the matrix cores.  precision 0: fp32 operands, the lowered matrix never leaves the compute unit; 1: operands rounded to bf16 (nearest even),
- * fp32 accumulation; 2: as 1 with the kernel matrix already converted - weights then points to
- * the sizes.wb_len 16-bit elements im2col_prepare_weights_bf16 wrote (same result, bit for bit,
- * without the conversion launch of every precision-1 call).  lowered: scratch of
- * sizes.lowered_bytes bytes (bf16: lowered matrix, then the partial sums of the product when the
- * contraction is split over workgroups; slices are added in a fixed order).  weights for
- * precision 0 and 1: fp32 in the K x C x kh x kw layout.  lowered must be 16-byte aligned, and so
- * must precision-2 weights.
+ * the matrix cores; the lowered matrix never leaves the compute unit.  precision 0: fp32 operands;
+ * 1: operands rounded to bf16 (nearest even), fp32 accumulation; 2: as 1 with the kernel matrix
+ * already converted - weights then points to the sizes.wb_len 16-bit elements
+ * im2col_prepare_weights_bf16 wrote (same result, bit for bit).  lowered: scratch of
+ * sizes.lowered_bytes bytes (bf16 calls keep the kernel matrix in its order of use there).
+ * weights for precision 0 and 1: fp32 in the K x C x kh x kw layout.  lowered must be 16-byte
+ * aligned, and so must precision-2 weights.
  * Errors: NULL, SHAPE (also a misaligned lowered), ALGO (precision), HIP.
  */
 int im2col_conv(const float *act, const cpoconv_shape *shape, const void *weights,

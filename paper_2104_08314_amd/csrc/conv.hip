@@ -26,7 +26,7 @@
 // The code is kept short (7 to 14 KB): a launch of one image runs for 5 to 20 us, of which fetching
 // instructions is a part; unrolling further or pipelining the windows too made such launches 2 to 5 us
 // slower and gained nothing at large batches.
-#include "common.hpp"
+#include "conv_tiles.hpp"
 
 #include <cmath>
 
@@ -34,19 +34,7 @@ namespace cpoconv {
 
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-constexpr int kXcds = 8;               // accelerator dies, each with an L2 of its own
 constexpr int kStep = 16;              // contraction indices of a step: four matrix instructions of four
-
-// Exact division of 0 <= x < 2^31 by a divisor the host knows: multiply and shift.
-struct Divisor {
-    uint32_t m, s;
-};
-__device__ __forceinline__ int quotient(int x, const Divisor &d)
-{
-    return static_cast<int>(__umulhi(static_cast<uint32_t>(x) << 1, d.m) >> d.s);
-}
 
 struct ConvArgs {
     int32_t C, K, Kpad, N;
@@ -71,82 +59,9 @@ struct ConvArgs {
     float *out;
 };
 
-__device__ __forceinline__ int lane_id() { return threadIdx.x & (kLanes - 1); }
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
-
-// Loads through a buffer descriptor: a 32-bit offset per lane and one per wavefront, no address
-// arithmetic in the vector ALU, and an offset past the end reads zero.
-template <bool kFar>
-struct Buffer {
-    typedef uint32_t Offset;
-    static constexpr Offset kNothing = ~Offset{0};   // past the end of every buffer
-    __amdgpu_buffer_rsrc_t rsrc;
-    __device__ __forceinline__ Buffer(const void *p, int64_t bytes)
-    {
-        const int64_t limit = 0xFFFFFFF0ll;
-        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<uint32_t>(bytes < limit ? bytes : limit), 0x00027000);
-    }
-    __device__ __forceinline__ float load1(Offset lane_offset, Offset offset) const
-    {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_offset, offset, 0));
-    }
-    __device__ __forceinline__ uint4v load4(Offset lane_offset, Offset offset) const
-    {
-        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_offset, offset, 0);
-    }
-    template <int N> __device__ __forceinline__ void load(float *f, Offset lane_offset, Offset offset) const
-    {
-        if constexpr (N == 1) {
-            f[0] = load1(lane_offset, offset);
-        } else if constexpr (N == 2) {
-            const uint2v v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane_offset, offset, 0);
-#pragma unroll
-            for (int i = 0; i < N; ++i) f[i] = __uint_as_float(v[i]);
-        } else {
-#pragma unroll
-            for (int i0 = 0; i0 < N; i0 += 4) {
-                const uint4v v = load4(lane_offset + 4 * i0, offset);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) f[i0 + i] = __uint_as_float(v[i]);
-            }
-        }
-    }
-};
-
-// The same for arrays that 32-bit offsets do not reach: 64-bit addresses, the range checked here.
-template <>
-struct Buffer<true> {
-    typedef uint64_t Offset;
-    static constexpr Offset kNothing = ~Offset{0};
-    const char *base;
-    uint64_t bytes;
-    __device__ __forceinline__ Buffer(const void *p, int64_t n) : base(static_cast<const char *>(p)), bytes(n < 0 ? 0 : n) {}
-    __device__ __forceinline__ float load1(Offset lane_offset, Offset offset) const
-    {
-        const bool inside = lane_offset < bytes && lane_offset + offset + 4 <= bytes;
-        return inside ? *reinterpret_cast<const float *>(base + lane_offset + offset) : 0.0f;
-    }
-    __device__ __forceinline__ uint4v load4(Offset lane_offset, Offset offset) const
-    {
-        uint4v v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(load1(lane_offset, offset + 4 * i));
-        return v;
-    }
-    template <int N> __device__ __forceinline__ void load(float *f, Offset lane_offset, Offset offset) const
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) f[i] = load1(lane_offset, offset + 4 * i);
-    }
-};
-
 // One step's weights of a lane: w[mt][j] for kernel kbase + m * MT + mt (m = lane % 16).  Matrix
-// instruction j of a whole step contracts the indices 16 * step + 4 * (lane / 16) + j - a lane's four
-// are consecutive -, of the last, partial step 16 * step + 4 * j + lane / 16, so that it takes as many
-// instructions as it has groups of four indices; indices past the chunk's last one have weight zero.
+// instruction j of a step contracts the indices 16 * step + 4 * (lane / 16) + j (a lane's four are
+// consecutive).
 template <int MT>
 struct Weights {
     float w[MT][4];
@@ -161,15 +76,6 @@ struct Weights {
             for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(w[mt][j]));
     }
 };
-
-// Tile of this workgroup.  Workgroups go to the XCDs in turn: the tile numbers (kernel block outermost)
-// are dealt so that an XCD holds a contiguous range of them - its L2 then fetches one stretch of the map
-// and, with eight kernel blocks or more, its share of the weights only.
-__device__ __forceinline__ int tile_number()
-{
-    const int issued = blockIdx.x, total = gridDim.x, xcd = issued % kXcds;
-    return xcd * (total / kXcds) + min(xcd, total % kXcds) + issued / kXcds;
-}
 
 constexpr int kChunk = 16;   // channels of a chunk at most
 
@@ -402,26 +308,12 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
 
 // ---- launch shape ----------------------------------------------------------------------------------
 
-constexpr int kComputeUnits = 256;
-constexpr int kLdsLimit = 160 * 1024;
-
 struct ConvPlan {
     int mt, t, sw, cc, waves;
     bool far;   // a tile's share of an array spans 4 GiB or more: the kernel with 64-bit addresses
     int rows, cols, tiles, strips, mblocks, tab_bytes, window_bytes, lds;
     double cost;
 };
-
-// window rows behind 16 * t positions of strips sw wide, over all tiles
-int window_rows(const Geometry &g, int nb, int sw)
-{
-    const int out_rows = std::min(nb % sw == 0 ? nb / sw : (nb - 2) / sw + 2, g.N * g.Oh);   // tiles start at multiples of nb
-    int rows = (out_rows - 1) * g.stride + g.kh;
-    // a tile that runs into the next image also spans the rows between the images' windows
-    const bool may_cross = g.N > 1 && (static_cast<int64_t>(g.Oh) * sw) % nb != 0;
-    if (may_cross) rows += ((out_rows + g.Oh - 2) / g.Oh) * std::max(0, g.Ih - g.Oh * g.stride);
-    return rows;
-}
 
 bool evaluate(const Geometry &g, bool dense, ConvPlan *p)
 {
@@ -498,6 +390,10 @@ ConvPlan conv_plan(const Geometry &g, bool dense)
                 }
         }
     }
+    if (best.cost < 0.0) {   // large strides: the least window there is
+        best.mt = best.t = best.sw = best.cc = best.waves = 1;
+        if (!evaluate(g, dense, &best)) best.cost = -1.0;
+    }
     return best;
 }
 
@@ -525,15 +421,6 @@ int launch(const ConvPlan &p, const ConvArgs &a, const char *name, hipStream_t s
     return CPOCONV_OK;
 }
 
-Divisor divisor(int d)
-{
-    Divisor r;
-    r.s = 0;
-    while ((1ll << r.s) < d) ++r.s;
-    r.m = static_cast<uint32_t>(((1ull << (31 + r.s)) + d - 1) / d);
-    return r;
-}
-
 ConvArgs make_args(const Geometry &g, const ConvPlan &p, bool dense)
 {
     ConvArgs a = {};
@@ -551,39 +438,58 @@ ConvArgs make_args(const Geometry &g, const ConvPlan &p, bool dense)
     return a;
 }
 
+// A launch for the whole batch; with huge strides, where the window of a tile over several images may fit no
+// LDS, one for every image.  fill(args, n): the arrays, from image n on.
+template <bool kDense, typename Fill>
+int launch_batch(const Geometry &g, const char *name, hipStream_t stream, const Fill &fill)
+{
+    auto go = [&](const Geometry &geometry, const ConvPlan &p, int n) {
+        ConvArgs a = make_args(geometry, p, kDense);
+        fill(a, n);
+        return launch<kDense>(p, a, name, stream);
+    };
+    const ConvPlan &p = cached_plan(g, kDense);
+    if (p.cost >= 0.0) return go(g, p, 0);
+    Geometry one = g;
+    one.N = 1;
+    const ConvPlan &q = cached_plan(one, kDense);
+    if (q.cost < 0.0) return CPOCONV_ERR_SHAPE;
+    for (int n = 0; n < g.N; ++n) {
+        const int rc = go(one, q, n);
+        if (rc != CPOCONV_OK) return rc;
+    }
+    return CPOCONV_OK;
+}
+
 }  // namespace
 
 int launch_conv_columns(const cpoconv_map &map, const ColumnEntry *columns, const Geometry &g, int algo, const float *wt, float *out,
                         hipStream_t stream)
 {
-    const ConvPlan &p = cached_plan(g, false);
-    if (p.cost < 0.0) return CPOCONV_ERR_SHAPE;
-    ConvArgs a = make_args(g, p, false);
-    a.algo = algo;
-    a.da_image = map.da_cap;
-    a.values = map.da;
-    a.columns = columns;
-    a.hdr = map.hdr;
-    a.weights = wt;
-    a.out = out;
-    return launch<false>(p, a, "spmv_conv", stream);
+    return launch_batch<false>(g, "spmv_conv", stream, [&](ConvArgs &a, int n) {
+        a.algo = algo;
+        a.da_image = map.da_cap;
+        a.values = map.da + n * map.da_cap;
+        a.columns = columns + static_cast<int64_t>(n) * g.C * g.Iw * column_bands(g);
+        a.hdr = map.hdr + n * 8;
+        a.weights = wt;
+        a.out = out + static_cast<int64_t>(n) * g.K * g.Oh * g.Ow;
+    });
 }
 
 int launch_conv_dense_f32(const float *act, const Producer &prod, const Geometry &g, const float *w, float *out, hipStream_t stream)
 {
-    const ConvPlan &p = cached_plan(g, true);
-    if (p.cost < 0.0) return CPOCONV_ERR_SHAPE;
-    ConvArgs a = make_args(g, p, true);
-    a.relu = prod.relu;
-    a.bias = prod.bias;
-    a.map_image = static_cast<int64_t>(g.C) * g.H * g.W;
-    a.map_c = g.channel_last ? 1 : g.H * g.W;
-    a.map_r = g.channel_last ? g.W * g.C : g.W;
-    a.map_x = g.channel_last ? g.C : 1;
-    a.values = act;
-    a.weights = w;
-    a.out = out;
-    return launch<true>(p, a, "im2col_conv_f32", stream);
+    return launch_batch<true>(g, "im2col_conv_f32", stream, [&](ConvArgs &a, int n) {
+        a.relu = prod.relu;
+        a.bias = prod.bias;
+        a.map_image = static_cast<int64_t>(g.C) * g.H * g.W;
+        a.map_c = g.channel_last ? 1 : g.H * g.W;
+        a.map_r = g.channel_last ? g.W * g.C : g.W;
+        a.map_x = g.channel_last ? g.C : 1;
+        a.values = act + n * a.map_image;
+        a.weights = w;
+        a.out = out + static_cast<int64_t>(n) * g.K * g.Oh * g.Ow;
+    });
 }
 
 }  // namespace cpoconv

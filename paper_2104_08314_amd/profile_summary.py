@@ -19,7 +19,8 @@ from collections import defaultdict
 csv.field_size_limit(1 << 30)
 
 OURS = ("encode_kernel", "encode_small_kernel", "encode_channel_kernel", "encode_channel64_kernel", "column_table_kernel",
-        "zero_fill_kernel", "conv_f32_kernel", "im2col_lower_kernel", "im2col_lower_direct_kernel", "gemm_bf16_kernel", "splitk_reduce_kernel", "prepare_weights_kernel", "prepare_weights_bf16_kernel")
+        "zero_fill_kernel", "conv_f32_kernel", "conv_bf16_kernel", "reorder_weights_kernel",
+        "prepare_weights_kernel", "prepare_weights_bf16_kernel")
 
 
 def _find(directory, suffix):
@@ -45,7 +46,7 @@ def short_name(name):
     if short == "conv_f32":
         m = re.search(r"_kernel<\s*\w+,\s*\w+,\s*(\w+)", name)
         return "im2col_conv_f32" if (m and m.group(1) in ("true", "1")) else "spmv_conv"
-    return short
+    return "im2col_conv_bf16" if short == "conv_bf16" else short
 
 
 def kernel_stats(directory):

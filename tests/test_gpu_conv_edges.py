@@ -1,7 +1,7 @@
-"""The fp32 matrix-core convolution at the edges of its tiles: kernels, channels, contraction indices and
+"""The matrix-core convolutions at the edges of its tiles: kernels, channels, contraction indices and
 positions that leave remainders, tiles that run from one image into the next, narrow maps, columns of
-several 64-row bands, arrays that 32-bit offsets do not reach.  Both readers (encoded map, dense map)
-against the direct convolution."""
+several 64-row bands, arrays that 32-bit offsets do not reach.  Encoded map, dense map in
+fp32 and in bf16, against the direct convolution."""
 import numpy as np
 import pytest
 import torch
@@ -11,6 +11,7 @@ from paper_2104_08314_amd import workloads
 
 pytestmark = pytest.mark.gpu
 FP32_TOL = 1e-5
+BF16_TOL = 2e-2   # operands of 8 significant bits
 
 # images, (C, H, W, K, kh, kw, stride, pad_h[, pad_w])
 CASES = [
@@ -24,6 +25,9 @@ CASES = [
     (2, (24, 130, 6, 16, 3, 3, 1, 1)),    # three bands of 64 padded rows
     (1, (70, 12, 14, 130, 1, 7, 1, 0, 3)),
     (1, (5, 20, 20, 16, 11, 11, 1, 5)),   # the largest kernel
+    (18, (3, 256, 256, 2, 11, 11, 250, 0)),   # a stride that leaves one output: windows of many images
+    (3, (2, 254, 254, 3, 3, 3, 85, 1)),
+    (6, (40, 9, 57, 40, 1, 3, 1, 0, 1)),   # strips wider than a wavefront's positions, taps of no kernel known
     (40, (160, 14, 14, 192, 3, 3, 1, 1)),  # more workgroups than the chip holds
 ]
 
@@ -49,13 +53,14 @@ def test_edges(api, n_images, shape):
     act, w = torch.from_numpy(acts).cuda(), torch.from_numpy(w_np).cuda()
     api.cpoconv_prepare_weights(w, shape, buf.wt)
     api.cps_encode_batch(act, shape, buf.cps, buf.scratch)
-    for run in (lambda: api.cps_conv_batch(buf.cps, shape, buf.wt, buf.out, buf.scratch),
-                lambda: api.cpo_encode_conv(act, shape, buf.cpo, buf.wt, buf.out, buf.scratch),
-                lambda: api.im2col_conv_batch(act, shape, n_images, w, buf.lowered, buf.out, 0)):
+    for run, tol in ((lambda: api.cps_conv_batch(buf.cps, shape, buf.wt, buf.out, buf.scratch), FP32_TOL),
+                     (lambda: api.cpo_encode_conv(act, shape, buf.cpo, buf.wt, buf.out, buf.scratch), FP32_TOL),
+                     (lambda: api.im2col_conv_batch(act, shape, n_images, w, buf.lowered, buf.out, 0), FP32_TOL),
+                     (lambda: api.im2col_conv_batch(act, shape, n_images, w, buf.lowered, buf.out, 1), BF16_TOL)):
         buf.out.fill_(float("nan"))
         run()
         got = buf.out.cpu().numpy().reshape(ref.shape)
-        assert np.abs(got - ref).max() <= FP32_TOL * max(np.abs(ref).max(), 1e-30)
+        assert np.abs(got - ref).max() <= tol * max(np.abs(ref).max(), 1e-30)
 
 
 def test_weights_past_4_gib(api):
@@ -67,8 +72,9 @@ def test_weights_past_4_gib(api):
     buf = api.LayerBuffers(shape)
     assert 4 * buf.wt.numel() > 1 << 32 and 4 * w.numel() > 1 << 32
     api.cpoconv_prepare_weights(w, shape, buf.wt)
-    for run in (lambda: api.cpo_encode_conv(act, shape, buf.cpo, buf.wt, buf.out, buf.scratch),
-                lambda: api.im2col_conv(act, shape, w, buf.lowered, buf.out, 0)):
+    for run, tol in ((lambda: api.cpo_encode_conv(act, shape, buf.cpo, buf.wt, buf.out, buf.scratch), FP32_TOL),
+                     (lambda: api.im2col_conv(act, shape, w, buf.lowered, buf.out, 0), FP32_TOL),
+                     (lambda: api.im2col_conv(act, shape, w, buf.lowered, buf.out, 1), BF16_TOL)):
         buf.out.fill_(float("nan"))
         run()
-        assert (buf.out.view(-1) - ref).abs().max() <= FP32_TOL * ref.abs().max()
+        assert (buf.out.view(-1) - ref).abs().max() <= tol * ref.abs().max()
