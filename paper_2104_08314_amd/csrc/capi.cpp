@@ -112,18 +112,16 @@ static void make_geometry(const cpoconv_shape *s, Geometry *g)
     int n = 0;
     for (int t = 0; t < s->kw; ++t) {
         if (count[t] == 0) continue;
-        g->type_id[g->n_types] = static_cast<uint8_t>(t);
-        g->type_begin[g->n_types] = static_cast<uint16_t>(n);
+        g->type_id[g->n_types] = t;
+        g->type_begin[g->n_types] = n;
         for (int j = 0; j < g->Iw; ++j) {
             if (type_of[j] != t) continue;
-            g->col_j[n] = static_cast<uint8_t>(j);
-            g->col_p0[n] = static_cast<uint8_t>(p0_of[j]);
-            g->col_what[n] = static_cast<uint8_t>(j - p0_of[j] * s->stride);
+            g->col[n] = static_cast<uint32_t>(j | p0_of[j] << 8 | (j - p0_of[j] * s->stride) << 16);
             ++n;
         }
         ++g->n_types;
     }
-    g->type_begin[g->n_types] = static_cast<uint16_t>(n);
+    g->type_begin[g->n_types] = n;
     g->n_cols = n;
     g->nop3 = (s->stride == 1 && s->pad_w == 0 && s->kw >= 2 && g->Ow >= 2) ? 1 : 0;
     g->top = -1;
@@ -133,6 +131,8 @@ static void make_geometry(const cpoconv_shape *s, Geometry *g)
         for (int i = 0; i < g->n_types; ++i)
             if (g->type_id[i] == top) { g->top = top; g->top_slot = i; }
     }
+    g->top_begin = g->top_slot >= 0 ? g->type_begin[g->top_slot] : kMaxCols + 1;
+    g->top_end = g->top_slot >= 0 ? g->type_begin[g->top_slot + 1] : 0;
 }
 
 int build_geometry(const cpoconv_shape *s, Geometry *g)
@@ -579,10 +579,10 @@ int cpoconv_geometry(const cpoconv_shape *shape, int32_t info[8], int32_t *col_j
     info[4] = g.n_cols; info[5] = g.n_types; info[6] = g.nop3; info[7] = g.top;
     for (int i = 0; i < g.n_types; ++i)
         for (int n = g.type_begin[i]; n < g.type_begin[i + 1]; ++n) {
-            col_j[n] = g.col_j[n];
+            col_j[n] = column_j(g, n);
             col_type[n] = g.type_id[i];
-            col_p0[n] = g.col_p0[n];
-            col_what[n] = g.col_what[n];
+            col_p0[n] = column_p0(g, n);
+            col_what[n] = column_what(g, n);
         }
     return CPOCONV_OK;
 }

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(kTableThreads) void column_table_kernel(const Geome
             int first[kColumnsAhead];   // the first 64 entries of every column: most columns have no more
 #pragma unroll
             for (int u = 0; u < kColumnsAhead; ++u) {
-                const int vi = min(v0 + u, type_end - 1), p0 = g.col_p0[vi];
+                const int vi = min(v0 + u, type_end - 1), p0 = column_p0(g, vi);
                 const int n = row[p0] + lane;
                 first[u] = n < row[p0 + 1] ? load_index(indices, n + in_shift, in16) : -1;
             }
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kTableThreads) void column_table_kernel(const Geome
             for (int u = 0; u < kColumnsAhead; ++u) {
                 const int vi = v0 + u;
                 if (vi >= type_end) break;
-                const int p0 = g.col_p0[vi], j = g.col_j[vi], what = g.col_what[vi];
+                const int p0 = column_p0(g, vi), j = column_j(g, vi), what = column_what(g, vi);
                 const int begin = row[p0], end = row[p0 + 1];   // the partition's NZEs: its columns in turn
                 int before = 0;                                 // NZEs of the partition's columns before this one
                 for (int n0 = begin; n0 < end; n0 += kLanes) {
@@ -199,10 +199,10 @@ __global__ __launch_bounds__(kTableThreads) void column_table_kernel(const Geome
         }
         // a partition's NZEs: its columns in turn
         for (int vi = g.type_begin[cps_top] + threadIdx.x; vi < g.type_begin[cps_top + 1]; vi += nthreads) {
-            int begin = bound[g.col_p0[vi]];
-            for (int prev = vi - 1; prev >= g.type_begin[cps_top] && g.col_p0[prev] == g.col_p0[vi]; --prev)
-                for (int b = 0; b < bands; ++b) begin += __popcll(rows[g.col_j[prev] * bands + b]);
-            run_begin[g.col_j[vi]] = begin;
+            int begin = bound[column_p0(g, vi)];
+            for (int prev = vi - 1; prev >= g.type_begin[cps_top] && column_p0(g, prev) == column_p0(g, vi); --prev)
+                for (int b = 0; b < bands; ++b) begin += __popcll(rows[column_j(g, prev) * bands + b]);
+            run_begin[column_j(g, vi)] = begin;
         }
     }
     __syncthreads();

@@ -30,12 +30,16 @@ struct Geometry {
     int32_t Kpad;                    // K rounded up to a multiple of 64
     int32_t N;                       // images in the launch (1 unless a batched entry point)
     int32_t channel_last;            // the dense input map is H x W x C instead of C x H x W
-    uint8_t type_id[kMaxTypes];      // present types, ascending
-    uint16_t type_begin[kMaxTypes + 1];  // column range of each present type
-    uint8_t col_j[kMaxCols];         // padded column
-    uint8_t col_p0[kMaxCols];        // first partition holding it
-    uint8_t col_what[kMaxCols];      // column inside that partition
+    // (whole words: a kernel reads them with scalar loads where the index is the wavefront's, and all of a
+    // column with one load where it is the lane's)
+    int32_t top_begin, top_end;          // column range of the type CPS packs, empty and past every column if none
+    int32_t type_id[kMaxTypes];          // present types, ascending
+    int32_t type_begin[kMaxTypes + 1];   // column range of each present type
+    uint32_t col[kMaxCols];              // padded column, first partition holding it << 8, column inside that partition << 16
 };
+__host__ __device__ inline int column_j(const Geometry &g, int i) { return static_cast<int>(g.col[i] & 255u); }
+__host__ __device__ inline int column_p0(const Geometry &g, int i) { return static_cast<int>(g.col[i] >> 8 & 255u); }
+__host__ __device__ inline int column_what(const Geometry &g, int i) { return static_cast<int>(g.col[i] >> 16); }
 
 // Where element (channel c, row hr, column jr) of one image's dense input map sits.
 __device__ __forceinline__ int64_t map_index(const Geometry &g, int c, int hr, int jr)

@@ -87,11 +87,17 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
     return v;
 }
 
-__device__ __forceinline__ int wave_sum(int v)
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_inclusive_sum(v), kLanes - 1); }
+
+// number of bits of mask below the lane
+__device__ __forceinline__ int rank_in(unsigned long long mask)
 {
-#pragma unroll
-    for (int d = kLanes / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kLanes);
-    return v;
+    return __builtin_amdgcn_mbcnt_hi(static_cast<unsigned>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<unsigned>(mask), 0u));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, int64_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<uint32_t>(bytes), 0x00027000);
 }
 
 __device__ __forceinline__ int bcast(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
@@ -122,7 +128,21 @@ __device__ __forceinline__ void poke(unsigned long long *p, unsigned long long v
 // up stores the same stamp in hdr[7].  A map is failed when the two agree.  Nothing has to be reset when
 // a call starts - a reset would race with units that give up at once - and a stamp left by an
 // earlier failed call never equals a later call's; the last unit clears such a leftover all the same.
-__device__ __forceinline__ int call_stamp(unsigned long long epoch) { return static_cast<int>(epoch % 0x7FFFFFull) + 1; }
+__device__ __forceinline__ int call_stamp(unsigned long long epoch) { return static_cast<int>(epoch & 0x3FFFFFull) + 1; }
+// epoch % (2^32 - 2) + 1 without a division: 2^32 leaves 2
+__device__ __forceinline__ unsigned long long call_tag(unsigned long long epoch)
+{
+    unsigned long long t = (epoch & 0xFFFFFFFFull) + 2ull * (epoch >> 32);
+    t = (t & 0xFFFFFFFFull) + 2ull * (t >> 32);
+    return (t >= 0xFFFFFFFEull ? t - 0xFFFFFFFEull : t) + 1ull;
+}
+// (a wavefront's own copy: what follows from it is scalar work)
+__device__ __forceinline__ unsigned long long read_epoch(const unsigned long long *p)
+{
+    const unsigned long long e = peek(p);
+    return static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<unsigned>(e >> 32))) << 32 |
+           static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<unsigned>(e)));
+}
 __device__ __forceinline__ void close_header(int32_t *hdr, int stamp, int in16)   // the last unit, also when it gives up
 {
     hdr[6] = (in16 ? 16 : 32) | (stamp << 8);
@@ -205,9 +225,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
     const int vb = plan.band_begin[b], ve = plan.band_begin[b + 1], nb = ve - vb;
     const int my_slot = plan.band_slot[b];
 
-    const unsigned long long epoch = peek(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
+    const unsigned long long epoch = read_epoch(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
     const int stamp = call_stamp(epoch);
-    const unsigned long long tag = kMode == kSinglePass ? epoch % 0xFFFFFFFEull + 1ull : kTagTwoLaunches;
+    const unsigned long long tag = kMode == kSinglePass ? call_tag(epoch) : kTagTwoLaunches;
     unsigned long long *flags = flags_all + 2 * static_cast<int64_t>(image) * units_stride;
 
     cpoconv_map map = maps;
@@ -225,11 +245,15 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
     const int col = lane & (CW - 1), rp = lane >> cw_log2;
     const bool col_ok = col < nb;
     const int vi = vb + (col_ok ? col : 0);               // this lane's column in stream order
-    const int jr = static_cast<int>(g.col_j[vi]) - g.pad_w;
+    const int jr = column_j(g, vi) - g.pad_w;
     const int IhP = g.Ih | 1;                             // odd column stride: conflict-free rows
     float *tile = lds + wave * (tile_floats + kLanes);
     int32_t *tblw = reinterpret_cast<int32_t *>(tile + tile_floats);
-    const float *map_in = act_all + static_cast<int64_t>(image) * g.C * g.H * g.W;
+    // (fewer than 2048 channels of at most 256 x 256 take this kernel: 32-bit offsets; past the end reads zero)
+    const __amdgpu_buffer_rsrc_t map_in =
+        buffer_of(act_all + static_cast<int64_t>(image) * g.C * g.H * g.W, static_cast<int64_t>(g.C) * g.H * g.W * 4);
+    const unsigned row_bytes = g.W * (g.channel_last ? g.C : 1) * 4u;
+    const unsigned at_col = map_index(g, c, 0, jr) * 4u;
     const float bias_c = (prod.relu && prod.bias != nullptr) ? prod.bias[c] : 0.0f;
 
     unsigned long long m[kMaskWords];   // bit h % 64 of word h / 64: padded row h of this lane's column holds an NZE
@@ -245,7 +269,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             for (int u = 0; u < kInFlight; ++u) {
                 const int h = h0 + u * RP + rp, hr = h - g.pad_h;
                 const bool ok = col_ok && h < h_end && hr >= 0 && hr < g.H;
-                v[u] = ok ? map_in[map_index(g, c, hr, jr)] : 0.0f;
+                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(map_in, ok ? at_col + hr * row_bytes : ~0u, 0, 0));
             }
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
@@ -262,8 +286,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
     wave_lds_fence();
 
     // ---- counts and offsets: lanes 0 .. nb-1 are the band's columns in stream order -------------------
-    const int top_begin = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot] : kMaxCols + 1;
-    const int top_end = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot + 1] : 0;
+    const int top_begin = cps ? g.top_begin : kMaxCols + 1;
+    const int top_end = cps ? g.top_end : 0;
     int cnt = 0, ecnt = 0;
     if (lane < nb) {
         const bool packed = vb + lane >= top_begin && vb + lane < top_end;
@@ -348,9 +372,9 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             }
         }
     }
-    ptr_off = wave_sum(ptr_off);
-    da_off = wave_sum(da_off);
-    in_off = wave_sum(in_off);
+    ptr_off = wave_total(ptr_off);
+    da_off = wave_total(da_off);
+    in_off = wave_total(in_off);
     // the bands of this channel: lane bb holds band bb
     int sib_n = 0, sib_i = 0, sib_p = 0;
     if (lane < B) {
@@ -435,7 +459,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             for (int w = 0; w < kMaskWords; ++w) {
                 if (w >= row_bands) continue;
                 const int n = __popcll(m[w]);
-                table[g.col_j[vi] * row_bands + w] =
+                table[column_j(g, vi) * row_bands + w] =
                     ColumnEntry{at, n, static_cast<uint32_t>(m[w]), static_cast<uint32_t>(m[w] >> 32)};
                 at += n;
             }
@@ -448,8 +472,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
     // ---- ptr of the band's types ------------------------------------------------------------------------
     if (!live && b == 0 && lane == 0) map.ptr[ptr_off] = CPOCONV_NPC;
     {
-        const int my_p0 = static_cast<int>(g.col_p0[vb + min(lane, nb - 1)]);
-        const int next_p0 = lane + 1 < nb ? static_cast<int>(g.col_p0[vb + lane + 1]) : -1;
+        const int my_p0 = column_p0(g, vb + min(lane, nb - 1));
+        const int next_p0 = lane + 1 < nb ? column_p0(g, vb + lane + 1) : -1;
         int seg = ptr_off + ptr_start;
         for (int i = 0; i < g.n_types; ++i) {
             const int tb = g.type_begin[i], te = g.type_begin[i + 1];
@@ -460,8 +484,8 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
             const int local = (ce == ve ? nnz_u : bcast(excl, ce - vb)) - local_before;
             const int t_before = my_slot == kWholeTypes ? 0 : type_before;
             const int t_total = my_slot == kWholeTypes ? local : type_total;
-            const int p_begin = has_first ? 0 : static_cast<int>(g.col_p0[cb]);
-            const int p_end = has_last ? g.Ow : static_cast<int>(g.col_p0[ce]);
+            const int p_begin = has_first ? 0 : column_p0(g, cb);
+            const int p_end = has_last ? g.Ow : column_p0(g, ce);
             const bool nop3 = g.nop3 && g.type_id[i] == 0;
             const bool entries = live && t_total > 0 && !nop3;        // the segment has its Ow cumulative entries
             if (live && has_first && lane == 0) {
@@ -505,7 +529,7 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
         const bool on = k < nb;
         const int src = on ? k : 0;
         int at_da = da_base + __shfl(excl, src, kLanes), at_in = in_base + __shfl(eexcl, src, kLanes);
-        const int what = static_cast<int>(g.col_what[vb + src]);
+        const int what = column_what(g, vb + src);
         const bool packed = on && vb + k >= top_begin && vb + k < top_end;
 #pragma unroll
         for (int w = 0; w < kMaskWords; ++w) {
@@ -566,9 +590,9 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     // image blockIdx.y of the launch: its map is image 0's advanced by the per-image capacities
     const int image = blockIdx.y;
     const float *__restrict__ act = act_all + static_cast<int64_t>(image) * g.C * g.H * g.W;
-    const unsigned long long epoch = peek(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
+    const unsigned long long epoch = read_epoch(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
     const int stamp = call_stamp(epoch);
-    const unsigned long long tag = kMode == kSinglePass ? epoch % 0xFFFFFFFEull + 1ull : kTagTwoLaunches;
+    const unsigned long long tag = kMode == kSinglePass ? call_tag(epoch) : kTagTwoLaunches;
     unsigned long long *flags = flags_all + 2 * static_cast<int64_t>(image) * units_stride;
     cpoconv_map map = maps;
     map.ptr += image * maps.ptr_cap;
@@ -594,8 +618,8 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     const int lane = lane_id(), wave = wave_id(), tid = threadIdx.x;
     const int Wt = g.W | 1;
     const int nchunks = (g.Ih + kChunk - 1) / kChunk;
-    const int top_begin = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot] : kMaxCols + 1;
-    const int top_end = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot + 1] : 0;
+    const int top_begin = cps ? g.top_begin : kMaxCols + 1;
+    const int top_end = cps ? g.top_end : 0;
     const float bias_c = (prod.relu && prod.bias != nullptr) ? prod.bias[c] : 0.0f;
 
     // rows wave, wave + 8, .. of the chunk: all of a wavefront's row loads are in flight before the
@@ -621,9 +645,9 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     // the tile's loads first, then everything that does not depend on them
     load_tile(0);
     if (tid < g.n_cols) {
-        col_jr[tid] = static_cast<uint8_t>(g.col_j[tid] - g.pad_w);
-        col_p0[tid] = g.col_p0[tid];
-        col_wh[tid] = g.col_what[tid];
+        col_jr[tid] = static_cast<uint8_t>(column_j(g, tid) - g.pad_w);
+        col_p0[tid] = column_p0(g, tid);
+        col_wh[tid] = column_what(g, tid);
     }
     if (tid < 4) chan_base[tid] = 0;
     __syncthreads();
@@ -660,7 +684,7 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
             ecnt_q[q][tid] = static_cast<uint16_t>((tid >= top_begin && tid < top_end) ? set4_entries(mask)
                                                                                       : __popcll(mask));
             if (table != nullptr) {   // the entry's rows now, its place in DA when that is known
-                ColumnEntry *e = table + g.col_j[tid] * row_bands + q;
+                ColumnEntry *e = table + column_j(g, tid) * row_bands + q;
                 e->count = __popcll(mask);
                 e->rows_lo = static_cast<uint32_t>(mask);
                 e->rows_hi = static_cast<uint32_t>(mask >> 32);
@@ -728,7 +752,7 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
             a2 += static_cast<int>(w1 & 0x1FFFFull);
             a0 += static_cast<int>((w1 >> 17) & 0x7FFFull);
         }
-        a0 = wave_sum(a0); a1 = wave_sum(a1); a2 = wave_sum(a2); failed = wave_sum(failed);
+        a0 = wave_total(a0); a1 = wave_total(a1); a2 = wave_total(a2); failed = wave_total(failed);
         if (lane == 0) {
             atomicAdd(&chan_base[0], a0);
             atomicAdd(&chan_base[1], a1);
@@ -773,7 +797,7 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
     // ---- for a convolution of the same call: the column table --------------------------------------
     if (table != nullptr) {
         if (tid < g.n_cols)
-            for (int q = 0; q < nchunks; ++q) table[g.col_j[tid] * row_bands + q].begin = da_off + col_excl[tid] + cnt_q[q][tid];
+            for (int q = 0; q < nchunks; ++q) table[column_j(g, tid) * row_bands + q].begin = da_off + col_excl[tid] + cnt_q[q][tid];
         for (int i = tid; i < g.Iw * row_bands; i += kThreads)
             if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0, 0u, 0u};
     }
@@ -852,25 +876,31 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
 
 // ---------------------------------------------------------------------------------------------
 // The workgroup-per-channel encoder for maps of at most 64 padded rows and 64 padded columns (every
-// layer of the workloads but the stems): the eight wavefronts share the channel's loads, the column
+// layer of the workloads but the stems): the wavefronts share the channel's loads, the column
 // bitmaps and the scatter, and in between EVERY wavefront does the channel's bookkeeping for itself,
 // lane = column in stream order - counts, prefix sums, type bases, offsets; only the look-back over
 // the channels before it is shared out (its words are read past the caches).  Almost nothing has to
-// be handed from wavefront to wavefront then, so the kernel has three workgroup barriers (tile
-// loaded, bitmaps built, look-back added up) where the general one has about fifteen, and a
-// workgroup lives two thirds as long.  The tables of a convolution that follows and the ptr segments
-// are written by the wavefront whose number the overlap type has (mod 8).
+// be handed from wavefront to wavefront then: two workgroup barriers (tile and bitmaps written,
+// look-back added up) where the general kernel has about fifteen.  The column table and the ptr
+// segments are written by the wavefront whose number the overlap type has (mod NW).
+//
+// With many channel-images this kernel is bound by the instructions it issues (128 x 56 x 56 at 32
+// images: 1170 vector and 1020 scalar instructions per wavefront took 51 us of the 55), hence: the
+// bitmaps come from the registers the rows were loaded into; rows and stores go through buffer
+// descriptors, whose range check stands for the conditions (a row outside the map reads zero, a lane
+// without an NZE stores past the end) and whose wavefront-wide offset for the 64-bit additions; ranks
+// are two mbcnt; loops over the overlap types run as often as there are types.
 // ---------------------------------------------------------------------------------------------
-template <int kMode, int NW>
+template <int kMode, int NW, bool kCps>
 __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const Geometry g, const float *__restrict__ act_all,
-                                                                   const Producer prod, const int cps,
+                                                                   const Producer prod,
                                                                    unsigned long long *__restrict__ ctrl,
                                                                    unsigned long long *__restrict__ flags_all,
                                                                    const int units_stride, const cpoconv_map maps,
                                                                    ColumnEntry *__restrict__ columns_all)
 {
-    extern __shared__ float tile[];                              // Ih x Wt, Wt odd: conflict-free column reads
-    __shared__ unsigned long long parts[kLanes];                 // a column's row bitmap: piece w (64 / NW bits) from wavefront w
+    extern __shared__ float tile[];                              // 64 padded rows x Wt, Wt odd: conflict-free column reads
+    __shared__ unsigned long long parts[kLanes];                 // row bitmap of a map column: piece w (64 / NW bits) from wavefront w
     constexpr int kT = NW * kLanes;                              // threads of the workgroup
     __shared__ int32_t stage[NW][kLanes];                        // one ptr segment under construction, per wavefront
     __shared__ int32_t chan_base[4];                             // ptr / DA / IN start of the channel, look-back failures
@@ -878,86 +908,82 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
     const int image = blockIdx.y, c = blockIdx.x;
     const int lane = lane_id(), tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-    const float *__restrict__ act = act_all + static_cast<int64_t>(image) * g.C * g.H * g.W;
-    unsigned long long *flags = flags_all + 2 * static_cast<int64_t>(image) * units_stride;
-    cpoconv_map map = maps;
-    map.ptr += image * maps.ptr_cap;
-    map.da += image * maps.da_cap;
-    const int in16 = maps.in_bits == 16 ? 1 : 0;
-    map.in = index_advance(maps.in, image * maps.in_cap, in16);
-    map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
-    map.hdr += image * 8;
-
     const int Wt = g.W | 1;
-    const int top_begin = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot] : kMaxCols + 1;
-    const int top_end = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot + 1] : 0;
-    const float bias_c = (prod.relu && prod.bias != nullptr) ? prod.bias[c] : 0.0f;
     constexpr int kRowsPerWave = kLanes / NW;   // 8 or 16: padded rows wave * kRowsPerWave .. belong to the wavefront
 
-    // ---- the channel into LDS: all of a wavefront's row loads in flight before the first store -----
+    const unsigned my_col = g.col[lane], next_col = g.col[lane + 1];   // (on their way with the map)
+
+    // ---- the channel into LDS, all of a wavefront's row loads in flight together, and the rows' share of the
+    // bitmaps from the registers -----------------------------------------------------------------------
     {
+        const int x_step = g.channel_last ? g.C : 1;
+        const int row_step = g.W * x_step;
+        const int first = wave * kRowsPerWave - g.pad_h;
+        const float *row = act_all + static_cast<int64_t>(image) * g.C * g.H * g.W + (g.channel_last ? c : static_cast<int64_t>(c) * g.H * g.W) +
+                           static_cast<int64_t>(first) * row_step;
+        const unsigned x_at = lane < g.W ? lane * x_step * 4u : ~0u;
         float v[kRowsPerWave];
 #pragma unroll
         for (int i = 0; i < kRowsPerWave; ++i) {
-            const int hr = wave * kRowsPerWave + i - g.pad_h;
-            v[i] = (hr >= 0 && hr < g.H && lane < g.W) ? act[map_index(g, c, hr, lane)] : 0.0f;
+            v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buffer_of(row, static_cast<unsigned>(first + i) < static_cast<unsigned>(g.H) ? row_step * 4 : 0), x_at, 0, 0));
+            row += row_step;
         }
+        if (prod.relu) {
+            const float bias_c = prod.bias != nullptr ? prod.bias[c] : 0.0f;
+            const unsigned in_row = lane < g.W ? ~0u : 0u;
 #pragma unroll
-        for (int i = 0; i < kRowsPerWave; ++i) {
-            const int hr = wave * kRowsPerWave + i - g.pad_h;
-            if (hr >= 0 && hr < g.H && lane < g.W) tile[hr * Wt + lane] = produced(v[i], prod, bias_c);
+            for (int i = 0; i < kRowsPerWave; ++i) {
+                const unsigned inside = static_cast<unsigned>(first + i) < static_cast<unsigned>(g.H) ? in_row : 0u;   // (zeros around the map stay zero)
+                v[i] = __uint_as_float(__float_as_uint(produced(v[i], prod, bias_c)) & inside);
+            }
+        }
+        unsigned bits = 0;
+#pragma unroll
+        for (int i = kRowsPerWave - 1; i >= 0; --i) bits = bits + bits + (is_nze(v[i]) ? 1u : 0u);
+        if constexpr (NW == 8) reinterpret_cast<uint8_t *>(parts)[lane * NW + wave] = static_cast<uint8_t>(bits);
+        else reinterpret_cast<uint16_t *>(parts)[lane * NW + wave] = static_cast<uint16_t>(bits);
+        if (lane < Wt) {
+            float *at = tile + wave * kRowsPerWave * Wt + lane;
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i) at[i * Wt] = v[i];
         }
     }
     // (read behind the tile's loads: loads complete in order, and this one goes past the caches)
-    const unsigned long long epoch = peek(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
-    const int stamp = call_stamp(epoch);
-    const unsigned long long tag = kMode == kSinglePass ? epoch % 0xFFFFFFFEull + 1ull : kTagTwoLaunches;
+    const unsigned long long epoch = read_epoch(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
     const bool col_ok = lane < g.n_cols;
-    const int my_jr = col_ok ? static_cast<int>(g.col_j[lane]) - g.pad_w : 0;
-    const int my_p0 = col_ok ? static_cast<int>(g.col_p0[lane]) : 0;
-    const int next_p0 = lane + 1 < g.n_cols ? static_cast<int>(g.col_p0[lane + 1]) : -1;
+    const int my_jr = col_ok ? static_cast<int>(my_col & 255u) - g.pad_w : 0;
+    const int my_what = col_ok ? my_col >> 16 : 0;
+    const int my_p0 = my_col >> 8 & 255u;
+    const int next_p0 = lane + 1 < g.n_cols ? static_cast<int>(next_col >> 8 & 255u) : -1;
+    const int stamp = call_stamp(epoch);
+    const unsigned long long tag = kMode == kSinglePass ? call_tag(epoch) : kTagTwoLaunches;
+    unsigned long long *flags = flags_all + 2 * static_cast<int64_t>(image) * units_stride;
     if (tid < 4) chan_base[tid] = 0;
     __syncthreads();
 
-    // ---- column bitmaps: the wavefront's eight rows of every column (lane = column), one byte each ---
-    {
-        unsigned bits = 0;
-        if (col_ok) {
-#pragma unroll
-            for (int i = 0; i < kRowsPerWave; ++i) {
-                const int hr = wave * kRowsPerWave + i - g.pad_h;
-                if (hr >= 0 && hr < g.H) bits |= static_cast<unsigned>(is_nze(tile[hr * Wt + my_jr])) << i;
-            }
-        }
-        if constexpr (NW == 8) reinterpret_cast<uint8_t *>(parts)[lane * NW + wave] = static_cast<uint8_t>(bits);
-        else reinterpret_cast<uint16_t *>(parts)[lane * NW + wave] = static_cast<uint16_t>(bits);
-    }
-    __syncthreads();
-
     // ---- from here on every wavefront keeps the channel's books itself: lane = column ---------------
-    const unsigned long long colmask = col_ok ? parts[lane] : 0ull;      // bit = padded row
+    const int top_begin = kCps ? g.top_begin : kMaxCols + 1;
+    const int top_end = kCps ? g.top_end : 0;
+    const unsigned long long colmask = col_ok ? parts[my_jr] : 0ull;     // bit = padded row
     const int cnt = __popcll(colmask);
-    const int ecnt = (lane >= top_begin && lane < top_end) ? set4_entries(colmask) : cnt;
-    const int incl = wave_inclusive_sum(cnt), eincl = wave_inclusive_sum(ecnt);
-    const int excl = incl - cnt, eexcl = eincl - ecnt;
-    const int nnz_c = __builtin_amdgcn_readlane(incl, kLanes - 1), in_c = __builtin_amdgcn_readlane(eincl, kLanes - 1);
-    int type_base[kMaxTypes + 1];
-#pragma unroll
-    for (int i = 0; i <= kMaxTypes; ++i) {
-        type_base[i] = nnz_c;
-        if (i <= g.n_types) {
-            const int b = g.type_begin[i];
-            if (b < g.n_cols) type_base[i] = __builtin_amdgcn_readlane(excl, b);
-        }
+    const int incl = wave_inclusive_sum(cnt), excl = incl - cnt;
+    const int nnz_c = __builtin_amdgcn_readlane(incl, kLanes - 1);
+    int eexcl = excl, in_c = nnz_c;
+    if constexpr (kCps) {
+        const int ecnt = (lane >= top_begin && lane < top_end) ? set4_entries(colmask) : cnt;
+        const int eincl = wave_inclusive_sum(ecnt);
+        eexcl = eincl - ecnt;
+        in_c = __builtin_amdgcn_readlane(eincl, kLanes - 1);
     }
+    auto before = [&](int column) { return column < g.n_cols ? __builtin_amdgcn_readlane(excl, column) : nnz_c; };   // NZEs before a column
     int ptr_c = 1;  // NPC
     if (nnz_c > 0) {
         ptr_c = 0;
-#pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types) continue;
-            if (g.nop3 && g.type_id[i] == 0) ptr_c += 3;
-            else ptr_c += (type_base[i + 1] > type_base[i]) ? 1 + g.Ow : 1;
+        int base = 0;
+        for (int i = 0; i < g.n_types; ++i) {
+            const int end = before(g.type_begin[i + 1]);
+            ptr_c += g.nop3 && g.type_id[i] == 0 ? 3 : (end > base ? 1 + g.Ow : 1);
+            base = end;
         }
     }
 
@@ -977,45 +1003,41 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
         w1 = peek(flags + 2 * tid + 1);
     }
 
-    // ... and while they travel, the scatter's items are prepared: columns wave, wave + 8, .. of the
-    // wavefront, lane = padded row; value, rank among the column's NZEs, and the IN entry with its rank
+    // ... and while they travel, the scatter's items are prepared: columns wave, wave + NW, .. of the
+    // wavefront, lane = padded row: the value, and in bits 0 - 15 of an integer four times its rank among the
+    // column's NZEs (no NZE: kNone, past the end of any channel's run).  Columns of the packed type have
+    // their IN entry above: bits 16 - 26 the entry, 27 - 31 its rank (no entry from this lane: kNoEntry).
     constexpr int kColsPerWave = kLanes / NW;   // n_cols <= 64
-    const int hr = lane - g.pad_h;
-    const bool row_ok = hr >= 0 && hr < g.H;
-    const unsigned long long below = (1ull << lane) - 1ull;
-    // (an item's integers share a register: rank in bits 0-6, rank of the IN entry + 1 in bits 7-13 -
-    // 0: no IN entry from this lane -, the entry itself, which fits 16 bits, above)
+    constexpr int kNone = 0xFFFC;
+    constexpr unsigned kNoEntry = 0x400u << 16;   // -1024: smaller than the negated index of any cell
+    const int place = my_jr | my_what << 8;
     float item_v[kColsPerWave];
-    int item_n[kColsPerWave];
+    unsigned item_n[kColsPerWave];
 #pragma unroll
     for (int n = 0; n < kColsPerWave; ++n) {
         const int vi = wave + n * NW;
         item_v[n] = 0.0f;
-        item_n[n] = 0;
+        item_n[n] = kNone;
         if (vi < g.n_cols) {
-            int entry, erank = -1;
-            const int jr = __builtin_amdgcn_readlane(my_jr, vi);
-            const float v = row_ok ? tile[hr * Wt + jr] : 0.0f;
+            const int at = __builtin_amdgcn_readlane(place, vi);
+            const float v = tile[lane * Wt + (at & 255)];
             const bool nz = is_nze(v);
             const unsigned long long mask = __ballot(nz);
-            const int rank = __popcll(mask & below);
-            const int index = static_cast<int>(g.col_what[vi]) + lane * g.kw;
+            const int rank = rank_in(mask);
             item_v[n] = v;
-            if (vi >= top_begin && vi < top_end) {
+            item_n[n] = nz ? rank * 4 : kNone;
+            if (kCps && vi >= top_begin && vi < top_end) {
                 // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
+                const int index = (at >> 8) + lane * g.kw;
                 const int pattern = static_cast<int>((mask >> (lane & ~3)) & 0xFull);
                 const int r = __popc(pattern & ((1 << (lane & 3)) - 1));   // rank inside the set
                 const bool emit = nz && r < 2;
-                const int among = __popcll(__ballot(emit) & below);
+                const int among = rank_in(__ballot(emit));
                 // first NZE of the set: its index (negated unless a pattern follows);
                 // second NZE: the pattern, or its own negated index
-                entry = __popc(pattern) >= 3 ? (r == 0 ? index : pattern) : -index;
-                if (emit) erank = among;
-            } else {
-                entry = index;
-                if (nz) erank = rank;
+                const int entry = __popc(pattern) >= 3 ? (r == 0 ? index : pattern) : -index;
+                item_n[n] |= emit ? static_cast<unsigned>(among) << 27 | (static_cast<unsigned>(entry) & 0x7FFu) << 16 : kNoEntry;
             }
-            item_n[n] = rank | ((erank + 1) << 7) | (entry << 16);
         }
     }
 
@@ -1049,16 +1071,27 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
                 a2 += static_cast<int>(p1 & 0x1FFFFull);
                 a0 += static_cast<int>((p1 >> 17) & 0x7FFFull);
             }
-        a0 = wave_sum(a0); a1 = wave_sum(a1); a2 = wave_sum(a2); bad = wave_sum(bad);
-        if (lane == 0 && (a0 | a1 | a2 | bad) != 0) {
-            atomicAdd(&chan_base[0], a0);
-            atomicAdd(&chan_base[1], a1);
-            atomicAdd(&chan_base[2], a2);
-            atomicAdd(&chan_base[3], bad);
+        if (wave * kLanes < c) {   // (a wavefront without a channel to read has nothing to add)
+            a0 = wave_total(a0); a1 = wave_total(a1); a2 = wave_total(a2);
+            const bool any_bad = __any(bad);
+            if (lane == 0) {
+                atomicAdd(&chan_base[0], a0);
+                atomicAdd(&chan_base[1], a1);
+                atomicAdd(&chan_base[2], a2);
+                if (any_bad) atomicAdd(&chan_base[3], 1);
+            }
         }
     }
     __syncthreads();
-    const int ptr_off = chan_base[0], da_off = chan_base[1], in_off = chan_base[2], failed = chan_base[3];
+    const int ptr_off = __builtin_amdgcn_readfirstlane(chan_base[0]), da_off = __builtin_amdgcn_readfirstlane(chan_base[1]),
+              in_off = __builtin_amdgcn_readfirstlane(chan_base[2]), failed = __builtin_amdgcn_readfirstlane(chan_base[3]);
+    cpoconv_map map = maps;
+    map.ptr += image * maps.ptr_cap;
+    map.da += image * maps.da_cap;
+    const int in16 = maps.in_bits == 16 ? 1 : 0;
+    map.in = index_advance(maps.in, image * maps.in_cap, in16);
+    map.chan_off += static_cast<int64_t>(image) * 3 * (g.C + 1);
+    map.hdr += image * 8;
     // the last channel has seen every other channel's lengths, so all of them have read the epoch:
     // it may move on (also after a failure, so that the words of this call are never taken for the next one's)
     if (tid == 0 && c == g.C - 1) {
@@ -1082,7 +1115,7 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
             map.hdr[0] = ptr_off + ptr_c;
             map.hdr[1] = da_off + nnz_c;
             map.hdr[2] = in_off + in_c;
-            map.hdr[3] = cps ? CPOCONV_ALGO_CPS : CPOCONV_ALGO_CPO;
+            map.hdr[3] = kCps ? CPOCONV_ALGO_CPS : CPOCONV_ALGO_CPO;
             map.hdr[4] = g.C;
             map.hdr[5] = g.Ow;
         }
@@ -1092,61 +1125,71 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
     if (columns_all != nullptr && wave == NW - 1) {
         ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
         if (col_ok)
-            row[g.col_j[lane]] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
+            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
         if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
     }
 
-    // ---- ptr: overlap type i by wavefront i mod 8 ----------------------------------------------------
     if (nnz_c == 0) {
         if (tid == 0) map.ptr[ptr_off] = CPOCONV_NPC;
         return;  // nothing to write to DA / IN
     }
+
+    // ---- scatter DA and IN from the prepared items ------------------------------------------------------
     {
-        int seg = ptr_off;
+        const __amdgpu_buffer_rsrc_t da = buffer_of(map.da + da_off, nnz_c * 4);
+        const __amdgpu_buffer_rsrc_t in = buffer_of(index_advance(map.in, in_off, in16), in_c << (2 - in16));
 #pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types) continue;
-            const int cb = g.type_begin[i], ce = g.type_begin[i + 1];
-            const int base = type_base[i];
-            const bool mine = (i & (NW - 1)) == wave;
-            if (g.nop3 && g.type_id[i] == 0) {
-                // [0, NZEs of the first column, NZEs of first + last column]
-                const int n1 = __builtin_amdgcn_readlane(incl, min(cb, kLanes - 1)) - base;
-                const int n2 = __builtin_amdgcn_readlane(incl, min(max(ce - 1, cb), kLanes - 1)) - base;
-                if (mine && lane == 0) { map.ptr[seg] = 0; map.ptr[seg + 1] = n1; map.ptr[seg + 2] = n2; }
-                seg += 3;
-                continue;
+        for (int n = 0; n < kColsPerWave; ++n) {
+            const int vi = wave + n * NW;
+            if (vi < g.n_cols) {
+                const int first = __builtin_amdgcn_readlane(excl, vi) * 4;
+                const unsigned at = kCps ? item_n[n] & 0xFFFFu : item_n[n];
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(item_v[n]), da, at, first, 0);
+                unsigned entry_at = at;
+                int entry = lane * g.kw + (__builtin_amdgcn_readlane(place, vi) >> 8), entry_first = first;
+                if constexpr (kCps) {
+                    entry_first = __builtin_amdgcn_readlane(eexcl, vi) * 4;
+                    if (vi >= top_begin && vi < top_end) {
+                        entry = static_cast<int>(item_n[n] << 5) >> 21;
+                        entry_at = entry != -1024 ? item_n[n] >> 27 << 2 : kNone;
+                    }
+                }
+                if (in16) __builtin_amdgcn_raw_buffer_store_b16(static_cast<short>(entry), in, entry_at >> 1, entry_first >> 1, 0);
+                else __builtin_amdgcn_raw_buffer_store_b32(static_cast<unsigned>(entry), in, entry_at, entry_first, 0);
             }
-            if (type_base[i + 1] == base) {
-                if (mine && lane == 0) map.ptr[seg] = CPOCONV_NPF;
-                seg += 1;
-                continue;
-            }
-            if (mine) {
-                int32_t *tblw = stage[wave];
-                tblw[lane] = -1;
-                wave_lds_fence();
-                // cumulative count after the last column first seen in each partition
-                if (lane >= cb && lane < ce && (lane + 1 == ce || next_p0 != my_p0)) tblw[my_p0] = incl - base;
-                wave_lds_fence();
-                if (lane == 0) map.ptr[seg] = g.type_id[i];
-                if (lane < g.Ow) map.ptr[seg + 1 + lane] = tblw[lane];
-                wave_lds_fence();
-            }
-            seg += 1 + g.Ow;
         }
     }
 
-    // ---- scatter DA and IN from the prepared items ------------------------------------------------------
-#pragma unroll
-    for (int n = 0; n < kColsPerWave; ++n) {
-        const int vi = wave + n * NW;
-        if (vi < g.n_cols) {
-            const int da_at = da_off + __builtin_amdgcn_readlane(excl, vi), in_at = in_off + __builtin_amdgcn_readlane(eexcl, vi);
-            const bool nz = is_nze(item_v[n]);
-            const int rank = item_n[n] & 127, erank = ((item_n[n] >> 7) & 127) - 1, entry = item_n[n] >> 16;
-            if (nz) map.da[da_at + rank] = item_v[n];
-            if (erank >= 0) store_index(map.in, in_at + erank, entry, in16);
+    // ---- ptr: overlap type i by wavefront i mod NW ----------------------------------------------------
+    {
+        int seg = ptr_off, base = 0;
+        for (int i = 0; i < g.n_types; ++i) {
+            const int cb = g.type_begin[i], ce = g.type_begin[i + 1], end = before(ce);
+            const bool mine = (i & (NW - 1)) == wave;
+            if (g.nop3 && g.type_id[i] == 0) {
+                // [0, NZEs of the first column, NZEs of first + last column]
+                if (mine && lane == 0) map.ptr[seg] = 0;
+                if (mine && lane == min(cb, kLanes - 1)) map.ptr[seg + 1] = incl - base;
+                if (mine && lane == min(max(ce - 1, cb), kLanes - 1)) map.ptr[seg + 2] = incl - base;
+                seg += 3;
+            } else if (end == base) {
+                if (mine && lane == 0) map.ptr[seg] = CPOCONV_NPF;
+                seg += 1;
+            } else {
+                if (mine) {
+                    int32_t *tblw = stage[wave];
+                    tblw[lane] = -1;
+                    wave_lds_fence();
+                    // cumulative count after the last column first seen in each partition
+                    if (lane >= cb && lane < ce && (lane + 1 == ce || next_p0 != my_p0)) tblw[my_p0] = incl - base;
+                    wave_lds_fence();
+                    if (lane == 0) map.ptr[seg] = g.type_id[i];
+                    if (lane < g.Ow) map.ptr[seg + 1 + lane] = tblw[lane];
+                    wave_lds_fence();
+                }
+                seg += 1 + g.Ow;
+            }
+            base = end;
         }
     }
 }
@@ -1157,8 +1200,9 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
 // 512-thread workgroup idle almost everywhere; here every step of a channel is a wavefront-wide
 // operation without workgroup barriers (column bitmaps with lane = column, prefix sums and type
 // bases by lane exchange, scatter with several columns per pass when the map has 32 or 16 rows).
-// Only the look-back is shared: the workgroup publishes its eight channels' lengths, all 512
-// threads read the channels before the group, and each wavefront adds its neighbours' lengths.
+// Only the look-back is shared: the workgroup publishes the sum of its eight channels' lengths (one
+// pair of words: with a pair per channel, 32 images of 512 x 7 x 7 spent most of their 36 us on reads past
+// the caches), its first wavefront adds up the groups before it, each wavefront its neighbours' lengths.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallTileBytes = 4096;
 // padded maps up to this many elements always take the one-wavefront-per-channel kernel; larger
@@ -1183,9 +1227,6 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
     const int c0 = blockIdx.x * kWaves, c = c0 + wave;
     const bool live = c < g.C;                         // wavefronts past the last channel only help with the look-back
     const float *__restrict__ act = act_all + static_cast<int64_t>(image) * g.C * g.H * g.W;
-    const unsigned long long epoch = peek(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
-    const int stamp = call_stamp(epoch);
-    const unsigned long long tag = kMode == kSinglePass ? epoch % 0xFFFFFFFEull + 1ull : kTagTwoLaunches;
     unsigned long long *flags = flags_all + 2 * static_cast<int64_t>(image) * units_stride;
     cpoconv_map map = maps;
     map.ptr += image * maps.ptr_cap;
@@ -1199,105 +1240,106 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
     const int per_wave = g.H * Wt + kLanes;            // floats of LDS per wavefront
     float *tile = tiles + wave * per_wave;
     int32_t *tblw = reinterpret_cast<int32_t *>(tile + g.H * Wt);
-    const int top_begin = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot] : kMaxCols + 1;
-    const int top_end = (cps && g.top_slot >= 0) ? g.type_begin[g.top_slot + 1] : 0;
+    const int top_begin = cps ? g.top_begin : kMaxCols + 1;
+    const int top_end = cps ? g.top_end : 0;
 
-    if (tid < 4) grp_base[tid] = 0;
-
-    // ---- the channel into LDS (coalesced), then its column bitmaps: lane = column in stream order ----
+    // ---- the channel into LDS (coalesced: whole rows side by side), then its column bitmaps: lane = column in
+    // stream order.  Eight loads of the wavefront are in flight before the first value is stored -----------
+    const unsigned my_col = g.col[lane], next_col = g.col[lane + 1];   // (on their way with the map)
     if (live) {
         const float bias_c = (prod.relu && prod.bias != nullptr) ? prod.bias[c] : 0.0f;
-        // eight loads of the wavefront in flight before the first value is stored
+        const int x_step = g.channel_last ? g.C : 1, rows_side = kLanes / g.W;
+        const int my_row = lane / g.W, my_x = lane - my_row * g.W;
+        const float *first = act + (g.channel_last ? c : static_cast<int64_t>(c) * g.H * g.W);
+        float *to = tile + my_row * Wt + my_x;
         constexpr int kInFlight = 8;
-        for (int i0 = lane; i0 < g.H * g.W; i0 += kInFlight * kLanes) {
+        for (int r0 = 0; r0 < g.H; r0 += kInFlight * rows_side) {
             float v[kInFlight];
+            const float *base = first + static_cast<int64_t>(r0) * g.W * x_step;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
-                const int i = i0 + u * kLanes, r = i / g.W;
-                v[u] = i < g.H * g.W ? act[map_index(g, c, r, i - r * g.W)] : 0.0f;
+                const int rows = min(rows_side, g.H - r0 - u * rows_side);   // of this load
+                v[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buffer_of(base, max(0, rows) * g.W * x_step * 4), lane * x_step * 4, 0, 0));
+                base += rows_side * g.W * x_step;
             }
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u) {
-                const int i = i0 + u * kLanes, r = i / g.W;
-                if (i < g.H * g.W) tile[r * Wt + (i - r * g.W)] = produced(v[u], prod, bias_c);
-            }
+            for (int u = 0; u < kInFlight; ++u)
+                if (my_row < min(rows_side, g.H - r0 - u * rows_side)) to[(r0 + u * rows_side) * Wt] = produced(v[u], prod, bias_c);
         }
     }
-    wave_lds_fence();
     const bool col_ok = live && lane < g.n_cols;
-    const int my_jr = col_ok ? static_cast<int>(g.col_j[lane]) - g.pad_w : 0;
-    const int my_p0 = col_ok ? static_cast<int>(g.col_p0[lane]) : 0;
-    const int next_p0 = (live && lane + 1 < g.n_cols) ? static_cast<int>(g.col_p0[lane + 1]) : -1;
-    unsigned long long colmask = 0;
-    if (col_ok)
-        for (int r = 0; r < g.H; ++r)
-            colmask |= static_cast<unsigned long long>(is_nze(tile[r * Wt + my_jr])) << (r + g.pad_h);   // bit = padded row
+    const int my_jr = col_ok ? static_cast<int>(my_col & 255u) - g.pad_w : 0;
+    const int my_what = col_ok ? my_col >> 16 : 0;
+    const int my_p0 = my_col >> 8 & 255u;
+    const int next_p0 = lane + 1 < g.n_cols ? static_cast<int>(next_col >> 8 & 255u) : -1;
+    // (read behind the tile's loads: loads complete in order, and this one goes past the caches)
+    const unsigned long long epoch = read_epoch(ctrl + 8 + image);   // one launch: the tag of its words; always: the call's stamp
+    const int stamp = call_stamp(epoch);
+    const unsigned long long tag = kMode == kSinglePass ? call_tag(epoch) : kTagTwoLaunches;
+    wave_lds_fence();
+    unsigned long long colmask = 0;   // bit = padded row
+    if (live) {
+        // (from the last row down: twice the bits, plus the row's)
+        const float *at = tile + my_jr;
+        unsigned hi = 0, lo = 0;
+        const int h = g.H;
+#pragma unroll 4
+        for (int r = h - 1; r >= 32; --r) hi = hi + hi + (is_nze(at[r * Wt]) ? 1u : 0u);
+#pragma unroll 8
+        for (int r = min(h, 32) - 1; r >= 0; --r) lo = lo + lo + (is_nze(at[r * Wt]) ? 1u : 0u);
+        colmask = col_ok ? (static_cast<unsigned long long>(hi) << 32 | lo) << g.pad_h : 0ull;
+    }
     const int cnt = __popcll(colmask);
     const int ecnt = (lane >= top_begin && lane < top_end) ? set4_entries(colmask) : cnt;
     const int incl = wave_inclusive_sum(cnt), eincl = wave_inclusive_sum(ecnt);
     const int excl = incl - cnt, eexcl = eincl - ecnt;
     const int nnz_c = __builtin_amdgcn_readlane(incl, kLanes - 1), in_c = __builtin_amdgcn_readlane(eincl, kLanes - 1);
-    int type_base[kMaxTypes + 1];
-#pragma unroll
-    for (int i = 0; i <= kMaxTypes; ++i) {
-        type_base[i] = nnz_c;
-        if (i <= g.n_types) {
-            const int b = g.type_begin[i];
-            if (b < g.n_cols) type_base[i] = __builtin_amdgcn_readlane(excl, b);
-        }
-    }
+    auto before = [&](int column) { return column < g.n_cols ? __builtin_amdgcn_readlane(excl, column) : nnz_c; };   // NZEs before a column
     int ptr_c = 1;  // NPC
     if (nnz_c > 0) {
         ptr_c = 0;
-#pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types) continue;
-            if (g.nop3 && g.type_id[i] == 0) ptr_c += 3;
-            else ptr_c += (type_base[i + 1] > type_base[i]) ? 1 + g.Ow : 1;
+        int base = 0;
+        for (int i = 0; i < g.n_types; ++i) {
+            const int end = before(g.type_begin[i + 1]);
+            ptr_c += g.nop3 && g.type_id[i] == 0 ? 3 : (end > base ? 1 + g.Ow : 1);
+            base = end;
         }
     }
 
-    // ---- look-back, shared by the workgroup -----------------------------------------------------
+    // ---- look-back: the first wavefront publishes the group's lengths and adds up the groups before it ----
     if (lane == 0) {
         grp[wave][0] = live ? ptr_c : 0;
         grp[wave][1] = live ? nnz_c : 0;
         grp[wave][2] = live ? in_c : 0;
-        if (kMode != kPublished && live) {
-            poke(flags + 2 * c, (tag << 32) | static_cast<unsigned>(nnz_c));
-            poke(flags + 2 * c + 1, (tag << 32) | static_cast<unsigned>(in_c) | (static_cast<unsigned>(ptr_c) << 17));
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const int group = blockIdx.x;
+        const bool member = lane < kWaves;
+        const int n = wave_total(member ? grp[lane][1] : 0), e = wave_total(member ? grp[lane][2] : 0), q = wave_total(member ? grp[lane][0] : 0);
+        if (kMode != kPublished && lane == 0) {
+            poke(flags + 2 * group, (tag << 32) | static_cast<unsigned>(n));
+            poke(flags + 2 * group + 1, (tag << 32) | static_cast<unsigned>(e) | (static_cast<unsigned>(q) << 17));
+        }
+        if (kMode == kPublishOnly) return;
+        int a0 = 0, a1 = 0, a2 = 0, bad = 0;
+        for (int other = lane; other < group; other += kLanes) {
+            const UnitLengths u = read_unit<kMode>(flags, other, tag);
+            if (!u.ok) { bad = 1; break; }
+            a0 += u.ptr_part;
+            a1 += u.nnz;
+            a2 += u.in;
+        }
+        a0 = wave_total(a0); a1 = wave_total(a1); a2 = wave_total(a2);
+        const bool any_bad = __any(bad);
+        if (lane == 0) {
+            grp_base[0] = a0;
+            grp_base[1] = a1;
+            grp_base[2] = a2;
+            grp_base[3] = any_bad ? 1 : 0;
         }
     }
     if (kMode == kPublishOnly) return;
-    __syncthreads();   // grp and grp_base written
-    {
-        int a0 = 0, a1 = 0, a2 = 0, failed = 0;
-        for (int cc = tid; cc < c0; cc += kThreads) {
-            unsigned long long w0, w1;
-            if (kMode == kPublished) {
-                w0 = flags[2 * cc];
-                w1 = flags[2 * cc + 1];
-            } else {
-                w0 = peek(flags + 2 * cc);
-                w1 = peek(flags + 2 * cc + 1);
-                for (int spin = 0; ((w0 >> 32) != tag || (w1 >> 32) != tag) && spin < kSpinLimit; ++spin) {
-                    __builtin_amdgcn_s_sleep(8);
-                    w0 = peek(flags + 2 * cc);
-                    w1 = peek(flags + 2 * cc + 1);
-                }
-            }
-            if ((w0 >> 32) != tag || (w1 >> 32) != tag || !lengths_plausible(w0, w1)) { failed = 1; break; }
-            a1 += static_cast<int>(w0 & 0xFFFFFFFFull);
-            a2 += static_cast<int>(w1 & 0x1FFFFull);
-            a0 += static_cast<int>((w1 >> 17) & 0x7FFFull);
-        }
-        a0 = wave_sum(a0); a1 = wave_sum(a1); a2 = wave_sum(a2); failed = wave_sum(failed);
-        if (lane == 0) {
-            atomicAdd(&grp_base[0], a0);
-            atomicAdd(&grp_base[1], a1);
-            atomicAdd(&grp_base[2], a2);
-            atomicAdd(&grp_base[3], failed);
-        }
-    }
     __syncthreads();
     // the last channel's group has seen every other channel's lengths: the epoch may move on (also
     // after a failure, so that the words of this call are never taken for the next one's)
@@ -1339,7 +1381,7 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
     if (columns_all != nullptr) {
         ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
         if (col_ok)
-            row[g.col_j[lane]] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
+            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
         if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
     }
 
@@ -1348,72 +1390,79 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
         if (lane == 0) map.ptr[ptr_off] = CPOCONV_NPC;
         return;
     }
+
+    // ---- scatter DA and IN: lane = (column of the pass, padded row); 1, 2 or 4 columns per pass.  A lane without
+    // an NZE stores past the end of the channel's run, where the range check drops it --------------------------
     {
-        int seg = ptr_off;
-#pragma unroll
-        for (int i = 0; i < kMaxTypes; ++i) {
-            if (i >= g.n_types) continue;
-            const int cb = g.type_begin[i], ce = g.type_begin[i + 1];
-            const int base = type_base[i];
-            if (g.nop3 && g.type_id[i] == 0) {
-                // [0, NZEs of the first column, NZEs of first + last column]
-                const int n1 = __builtin_amdgcn_readlane(incl, min(cb, kLanes - 1)) - base;
-                const int n2 = __builtin_amdgcn_readlane(incl, min(max(ce - 1, cb), kLanes - 1)) - base;
-                if (lane == 0) { map.ptr[seg] = 0; map.ptr[seg + 1] = n1; map.ptr[seg + 2] = n2; }
-                seg += 3;
-                continue;
+        const int rows_log2 = g.Ih <= 16 ? 4 : (g.Ih <= 32 ? 5 : 6);
+        const int sub = lane >> rows_log2, h = lane & ((1 << rows_log2) - 1);     // h: padded row
+        // rows of the lane's column above its own
+        const unsigned long long below = ((1ull << h) - 1ull) << (sub << rows_log2);
+        const int hr = h - g.pad_h;
+        const bool row_ok = hr >= 0 && hr < g.H;
+        const float *from = tile + (row_ok ? hr : 0) * Wt;
+        // what a lane needs of its column: map column, column inside the partition, NZEs and IN entries before it
+        // (maps of this kernel have at most 1024 elements)
+        const unsigned mine = my_jr | my_what << 6 | excl << 10;
+        const __amdgpu_buffer_rsrc_t da = buffer_of(map.da + da_off, nnz_c * 4);
+        const __amdgpu_buffer_rsrc_t in = buffer_of(index_advance(map.in, in_off, in16), in_c << (2 - in16));
+#pragma unroll 2
+        for (int v0 = 0; v0 < g.n_cols; v0 += kLanes >> rows_log2) {
+            const int vi = v0 + sub;
+            const bool on = vi < g.n_cols;
+            const unsigned column = __shfl(mine, on ? vi : 0, kLanes);
+            const float v = from[column & 63u];
+            const bool nz = on && row_ok && is_nze(v);
+            const unsigned long long all = __ballot(nz);
+            const int rank = __popcll(all & below);
+            const unsigned at = (column >> 10) + rank;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), da, nz ? at * 4 : ~3u, 0, 0);
+            int entry = static_cast<int>(column >> 6 & 15u) + h * g.kw;
+            unsigned entry_at = nz ? at : ~0u >> 2;
+            if (cps) {
+                const int at_in = __shfl(eexcl, on ? vi : 0, kLanes);
+                const bool packed = on && vi >= top_begin && vi < top_end;
+                // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
+                const int pattern = static_cast<int>((all >> (lane & ~3)) & 0xFull);
+                const int r = __popc(pattern & ((1 << (h & 3)) - 1));   // rank inside the set
+                const bool emit = packed && nz && r < 2;
+                const int erank = __popcll(__ballot(emit) & below);
+                if (nz) entry_at = at_in + rank;
+                if (packed) {
+                    entry = __popc(pattern) >= 3 ? (r == 0 ? entry : pattern) : -entry;
+                    entry_at = emit ? at_in + erank : ~0u >> 2;
+                }
             }
-            if (type_base[i + 1] == base) {
-                if (lane == 0) map.ptr[seg] = CPOCONV_NPF;
-                seg += 1;
-                continue;
-            }
-            tblw[lane] = -1;
-            wave_lds_fence();
-            // cumulative count after the last column first seen in each partition
-            if (lane >= cb && lane < ce && (lane + 1 == ce || next_p0 != my_p0)) tblw[my_p0] = incl - base;
-            wave_lds_fence();
-            if (lane == 0) map.ptr[seg] = g.type_id[i];
-            if (lane < g.Ow) map.ptr[seg + 1 + lane] = tblw[lane];
-            wave_lds_fence();
-            seg += 1 + g.Ow;
+            if (in16) __builtin_amdgcn_raw_buffer_store_b16(static_cast<short>(entry), in, entry_at * 2, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b32(static_cast<unsigned>(entry), in, entry_at * 4, 0, 0);
         }
     }
 
-    // ---- scatter DA and IN: lane = (column of the pass, padded row); 1, 2 or 4 columns per pass -----
-    const int rows_pass = g.Ih <= 16 ? 16 : (g.Ih <= 32 ? 32 : 64);
-    const int cols_pass = kLanes / rows_pass;
-    const int sub = lane / rows_pass, h = lane - sub * rows_pass;     // h: padded row
-    const unsigned long long sub_bits = rows_pass == 64 ? ~0ull : ((1ull << rows_pass) - 1ull);
-    const unsigned long long below = (1ull << h) - 1ull;
-    const int hr = h - g.pad_h;
-    const bool row_ok = hr >= 0 && hr < g.H;
-    for (int v0 = 0; v0 < g.n_cols; v0 += cols_pass) {
-        const int vi = v0 + sub;
-        const bool on = vi < g.n_cols;
-        const int src = on ? vi : 0;
-        const int jr = __shfl(my_jr, src, kLanes);
-        const int at_da = da_off + __shfl(excl, src, kLanes), at_in = in_off + __shfl(eexcl, src, kLanes);
-        const int what = on ? static_cast<int>(g.col_what[vi]) : 0;
-        const float v = (on && row_ok) ? tile[hr * Wt + jr] : 0.0f;
-        const bool nz = is_nze(v);
-        const unsigned long long all = __ballot(nz);
-        const unsigned long long mask = (all >> (sub * rows_pass)) & sub_bits;
-        const int rank = __popcll(mask & below);
-        const int index = what + h * g.kw;
-        if (nz) map.da[at_da + rank] = v;
-        const bool packed = on && vi >= top_begin && vi < top_end;
-        // set4 of Algorithm 3: the four padded rows 4*(h/4) .. +3
-        const int pattern = static_cast<int>((mask >> (h & ~3)) & 0xFull);
-        const int r = __popc(pattern & ((1 << (h & 3)) - 1));   // rank inside the set
-        const bool emit = packed && nz && r < 2;
-        const unsigned long long emits = (__ballot(emit) >> (sub * rows_pass)) & sub_bits;
-        const int erank = __popcll(emits & below);
-        const int entry = __popc(pattern) >= 3 ? (r == 0 ? index : pattern) : -index;
-        if (packed) {
-            if (emit) store_index(map.in, at_in + erank, entry, in16);
-        } else if (nz) {
-            store_index(map.in, at_in + rank, index, in16);
+    {
+        int seg = ptr_off, base = 0;
+        for (int i = 0; i < g.n_types; ++i) {
+            const int cb = g.type_begin[i], ce = g.type_begin[i + 1], end = before(ce);
+            if (g.nop3 && g.type_id[i] == 0) {
+                // [0, NZEs of the first column, NZEs of first + last column]
+                if (lane == 0) map.ptr[seg] = 0;
+                if (lane == min(cb, kLanes - 1)) map.ptr[seg + 1] = incl - base;
+                if (lane == min(max(ce - 1, cb), kLanes - 1)) map.ptr[seg + 2] = incl - base;
+                seg += 3;
+            } else if (end == base) {
+                if (lane == 0) map.ptr[seg] = CPOCONV_NPF;
+                seg += 1;
+            } else {
+                tblw[lane] = -1;
+                wave_lds_fence();
+                // cumulative count after the last column first seen in each partition
+                if (lane >= cb && lane < ce && (lane + 1 == ce || next_p0 != my_p0)) tblw[my_p0] = incl - base;
+                wave_lds_fence();
+                if (lane == 0) map.ptr[seg] = g.type_id[i];
+                if (lane < g.Ow) map.ptr[seg + 1 + lane] = tblw[lane];
+                wave_lds_fence();
+                seg += 1 + g.Ow;
+            }
+            base = end;
         }
     }
 }
@@ -1476,7 +1525,7 @@ bool build_bands(const Geometry &g, int cpb, EncodePlan *plan)
         const int head = nbands;
         for (int start = tb; start < te;) {
             int end = std::min(te, start + size);
-            while (end < te && g.col_p0[end] == g.col_p0[end - 1]) ++end;
+            while (end < te && column_p0(g, end) == column_p0(g, end - 1)) ++end;
             if (end - start > kLanes || nbands >= kMaxBands) return false;
             p.band_begin[nbands] = static_cast<uint16_t>(start);
             p.band_slot[nbands] = static_cast<uint8_t>(i);
@@ -1502,7 +1551,7 @@ EncodePlan make_encode_plan(const Geometry &g, bool *single_pass)
     int group = 1;   // columns sharing a first partition stay in one band: leave room for the largest group
     for (int i = 0; i < g.n_types; ++i)
         for (int n = g.type_begin[i] + 1, run = 1; n < g.type_begin[i + 1]; ++n) {
-            run = g.col_p0[n] == g.col_p0[n - 1] ? run + 1 : 1;
+            run = column_p0(g, n) == column_p0(g, n - 1) ? run + 1 : 1;
             group = std::max(group, run);
         }
     // fewest bands first (widest bands the LDS budget allows; if those are too many, up to a full
@@ -1559,7 +1608,13 @@ static bool use_bands(const Geometry &g)
     return g.H * g.W >= 128 * 128 ? channel_images < 2048 : (channel_images < 32 && g.H * g.W >= 64 * 64);
 }
 
-static bool channels_single_pass(const Geometry &g) { return g.C <= kUnitsPerImage && g.N <= kSinglePassImages; }
+static bool use_small(const Geometry &g);
+
+static bool channels_single_pass(const Geometry &g)
+{
+    const int units = use_small(g) ? (g.C + kWaves - 1) / kWaves : g.C;
+    return units <= kUnitsPerImage && g.N <= kSinglePassImages;
+}
 
 // look-back words of a call that takes two launches (behind the fixed region)
 int64_t encode_call_flags_bytes(const Geometry &g)
@@ -1611,11 +1666,14 @@ static int launch_encode_bands(const float *act, const Producer &prod, const Geo
 // A wavefront walks its channel's rows alone, which costs latency on the larger of the small maps:
 // those take the one-wavefront-per-channel kernel only once workgroups of the other kernel would
 // queue for a compute unit.
+// (the kernels for maps of at most 64 x 64 padded cells address the elements of a row with 32 bits)
+static bool row_offsets_fit(const Geometry &g) { return !g.channel_last || g.C < (1 << 24); }
+
 static bool use_small(const Geometry &g)
 {
     const size_t small_tile = static_cast<size_t>(g.H) * (g.W | 1) * sizeof(float);
     const bool worth = g.Ih * g.Iw <= kSmallAlways || static_cast<int64_t>(g.N) * g.C >= kSmallFromChannels;
-    return g.Ih <= kLanes && g.Iw <= kLanes && small_tile <= kSmallTileBytes && worth;
+    return g.Ih <= kLanes && g.Iw <= kLanes && small_tile <= kSmallTileBytes && worth && row_offsets_fit(g);
 }
 
 int launch_encode(const float *act, const Producer &prod, const Geometry &g, const cpoconv_map &map, int algo,
@@ -1659,30 +1717,32 @@ int launch_encode(const float *act, const Producer &prod, const Geometry &g, con
         CPOCONV_HIP_TRY(hipGetLastError());
         return CPOCONV_OK;
     }
-    if (g.Ih <= kLanes && g.Iw <= kLanes) {
+    if (g.Ih <= kLanes && g.Iw <= kLanes && row_offsets_fit(g)) {
         // maps of at most 64 x 64 padded cells: the variant whose wavefronts keep their own books
-        const size_t lds64 = static_cast<size_t>(g.H) * (g.W | 1) * sizeof(float);
+        const size_t lds64 = static_cast<size_t>(kLanes) * (g.W | 1) * sizeof(float);
         // Launches with many channel-images run four wavefronts per workgroup: twice the workgroups in
         // flight on a compute unit, half the copies of the per-wavefront bookkeeping (few channel-images:
         // eight wavefronts, the shorter life of a single workgroup counts).
         const bool narrow = static_cast<int64_t>(g.C) * g.N >= kNarrowFrom;
 #define CPOCONV_ENCODE64(MODE, NW, ...) \
-    hipLaunchKernelGGL((encode_channel64_kernel<MODE, NW>), dim3(g.C, g.N), dim3(NW * kLanes), lds64, stream, g, act, prod, cps, ctrl, \
-                       flags, units_stride, map, __VA_ARGS__)
+    if (cps) hipLaunchKernelGGL((encode_channel64_kernel<MODE, NW, true>), dim3(g.C, g.N), dim3(NW * kLanes), lds64, stream, g, act, prod, \
+                                ctrl, flags, units_stride, map, __VA_ARGS__); \
+    else hipLaunchKernelGGL((encode_channel64_kernel<MODE, NW, false>), dim3(g.C, g.N), dim3(NW * kLanes), lds64, stream, g, act, prod, \
+                            ctrl, flags, units_stride, map, __VA_ARGS__)
         if (single) {
             KernelTimer timer("encode", stream);
-            if (narrow) CPOCONV_ENCODE64(kSinglePass, 4, columns);
-            else CPOCONV_ENCODE64(kSinglePass, 8, columns);
+            if (narrow) { CPOCONV_ENCODE64(kSinglePass, 4, columns); }
+            else { CPOCONV_ENCODE64(kSinglePass, 8, columns); }
         } else {
             {
                 KernelTimer timer("encode_count", stream);
-                if (narrow) CPOCONV_ENCODE64(kPublishOnly, 4, static_cast<ColumnEntry *>(nullptr));
-                else CPOCONV_ENCODE64(kPublishOnly, 8, static_cast<ColumnEntry *>(nullptr));
+                if (narrow) { CPOCONV_ENCODE64(kPublishOnly, 4, static_cast<ColumnEntry *>(nullptr)); }
+                else { CPOCONV_ENCODE64(kPublishOnly, 8, static_cast<ColumnEntry *>(nullptr)); }
             }
             CPOCONV_HIP_TRY(hipGetLastError());
             KernelTimer timer("encode", stream);
-            if (narrow) CPOCONV_ENCODE64(kPublished, 4, columns);
-            else CPOCONV_ENCODE64(kPublished, 8, columns);
+            if (narrow) { CPOCONV_ENCODE64(kPublished, 4, columns); }
+            else { CPOCONV_ENCODE64(kPublished, 8, columns); }
         }
 #undef CPOCONV_ENCODE64
         CPOCONV_HIP_TRY(hipGetLastError());
