@@ -212,7 +212,6 @@ __global__ __launch_bounds__(kTableThreads) void column_table_kernel(const Geome
         for (int n = j * bands; n < i; ++n) before += __popcll(rows[n]);
         ColumnEntry entry;
         entry.begin = run_begin[j] + before;
-        entry.count = __popcll(rows[i]);
         entry.rows_lo = static_cast<uint32_t>(rows[i]);
         entry.rows_hi = static_cast<uint32_t>(rows[i] >> 32);
         out[i] = entry;

@@ -53,7 +53,6 @@ __device__ __forceinline__ int64_t map_index(const Geometry &g, int c, int hr, i
 // its entries; those of a column outside the streams (padding, or under no kernel position) are empty.
 struct ColumnEntry {
     int32_t begin;             // absolute offset in DA
-    int32_t count;             // NZEs (= set bits)
     uint32_t rows_lo, rows_hi; // bit r: row 64 * band + r holds an NZE
 };
 

@@ -15,13 +15,14 @@
 // sums; at the 40 to 85 % zeros of these maps the product over expanded windows is ahead of that
 // everywhere.
 //
-// Work split: a workgroup owns 16 * MT kernels x 16 * T positions; its wavefronts take the chunks of
-// input channels in turn and keep the sums of the whole tile each, added through LDS in wavefront order
-// at the end (results are repeatable).  Per chunk a wavefront fills a window of its own (nobody else
-// reads it: no barrier, and while one wavefront waits for its window another one multiplies) and
-// multiplies it.  Weights go from memory straight to registers, one to four steps ahead - a lane's MT
-// kernels or its four contraction indices are consecutive -, because one operand register feeds 32
-// cycles of matrix work per position tile: LDS could not make them cheaper.
+// Work split: a tile is 16 * MT kernels x 16 * T positions.  A wavefront has a tile of its own, or the
+// wavefronts of a workgroup share one: they take the chunks of input channels in turn and their sums are
+// added through LDS in wavefront order at the end (results are repeatable).  Per chunk a wavefront fills a
+// window of its own (nobody else reads it: no barrier, and while one wavefront waits for its window another
+// one multiplies) and multiplies it.  Weights go from memory straight to registers, one to four steps ahead
+// - a lane's MT kernels or its four contraction indices are consecutive -, because one operand register
+// feeds 32 cycles of matrix work per position tile: LDS could not make them cheaper; the values of the next
+// step leave LDS while this one multiplies.
 //
 // The code is kept short (7 to 14 KB): a launch of one image runs for 5 to 20 us, of which fetching
 // instructions is a part; unrolling further or pipelining the windows too made such launches 2 to 5 us
@@ -44,6 +45,7 @@ struct ConvArgs {
     int32_t sets;                      // ceil(cells / 64)
     int32_t cc, nchunks;               // channels of a chunk, chunks
     int32_t tiles, per_m;              // tiles of a strip, of all strips
+    int32_t whole_blocks;              // workgroups whose wavefronts have a tile each
     int32_t tab_bytes, window_bytes;   // LDS: offset table, then a window per wavefront
     int32_t bands;                     // 64-row bands of a padded column
     int32_t algo;                      // columns: what hdr[3] has to say
@@ -95,7 +97,11 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
     char *window = smem + a.tab_bytes + wave * a.window_bytes;
     const int stride_c = a.cells * 4;
 
-    const int number = tile_number();
+    // the last workgroups share a tile: their wavefronts take the chunks in turn
+    const bool shared = static_cast<int>(blockIdx.x) >= a.whole_blocks;
+    const int first_chunk = shared ? wave : 0, stride_chunk = shared ? nwaves : 1;
+    const int number = shared ? a.whole_blocks * nwaves + dealt(blockIdx.x - a.whole_blocks, gridDim.x - a.whole_blocks)
+                              : dealt(blockIdx.x, a.whole_blocks) * nwaves + wave;
     const int mb = quotient(number, a.by_per_m), in_m = number - mb * a.per_m;
     const int strip = quotient(in_m, a.by_tiles), tile = in_m - strip * a.tiles;
     const int kbase = mb * 16 * MT, p0 = tile * 16 * T, x0 = strip * a.SW;
@@ -128,17 +134,24 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
         }
     };
     W w[D];
-    const uint32_t q_first = static_cast<uint32_t>(wave) * a.cc * a.taps;
+    const uint32_t q_first = static_cast<uint32_t>(first_chunk) * a.cc * a.taps;
 #pragma unroll
     for (int d = 0; d < D - 1; ++d) load(w[d], q_first + d * kStep);   // (past a short chunk: not used, past the end: zeros)
 
-    // where the lane's positions start in the window
+    // where the lane's positions start in the window, and in the output (at kernel kbase + 4 * kk * MT; less than
+    // nothing: nowhere)
+    const int64_t plane = static_cast<int64_t>(a.Oh) * a.Ow;
     int base[T];
+    int64_t to[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int p = in_row0 + t * 16 + n, row = quotient(p, a.by_SW), image = quotient(y0 + row, a.by_Oh);
         const int y = y0 + row - image * a.Oh, x = p - row * a.SW;
-        base[t] = p0 + t * 16 + n < positions ? ((image * a.Ih + y * a.stride - top) * a.cols + x * a.stride) * 4 : 0;
+        const bool exists = p0 + t * 16 + n < positions;
+        base[t] = exists ? ((image * a.Ih + y * a.stride - top) * a.cols + x * a.stride) * 4 : 0;
+        bool ok = exists && x0 + x < a.Ow;
+        if constexpr (!kDense) ok = ok && !map_unusable(a.hdr, min(image0 + image, a.N - 1), a.algo);
+        to[t] = ok ? (static_cast<int64_t>(image0 + image) * a.K + kbase + 4 * kk * MT) * plane + y * a.Ow + x0 + x : -1;
     }
     const int chunk_q = a.cc * a.taps;
     auto window_offset = [&](int q) __attribute__((always_inline)) {
@@ -158,63 +171,93 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
 #pragma unroll
         for (int t = 0; t < T; ++t) acc[mt][t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
+    // ---- a cell of the window: where it comes from (past the end: no source, reads zero) and goes to, the same
+    // for every chunk ------------------------------------------------------------------------------------
+    struct Cell {
+        Offset from, da;        // columns: da, the cell's image in DA
+        int to, row;
+        bool inside, ok;
+    };
+    auto cell_of = [&](int i) __attribute__((always_inline)) {
+        Cell cell = {};
+        int r, q;
+        if constexpr (kDense) { r = quotient(i, a.by_line); q = i - r * a.cols; }
+        else { q = quotient(i, a.by_line); r = i - q * a.rows; }
+        const int v = top + r, image = quotient(v, a.by_Ih), row = v - image * a.Ih, j = x0 * a.stride + q;
+        cell.inside = i < a.cells;
+        cell.to = (r * a.cols + q) * 4;
+        cell.ok = cell.inside && image0 + image < a.N && j < a.Iw;
+        if constexpr (kDense) {
+            const int hr = row - a.pad_h, jr = j - a.pad_w;
+            cell.ok = cell.ok && hr >= 0 && hr < a.H && jr >= 0 && jr < a.W;
+            cell.from = (image * static_cast<Offset>(a.map_image) + static_cast<Offset>(hr) * a.map_r + static_cast<Offset>(jr) * a.map_x) * 4u;
+        } else {
+            cell.row = row & 63;
+            cell.from = ((static_cast<Offset>(image) * a.C * a.Iw + j) * a.bands + (row >> 6)) * sizeof(ColumnEntry);
+            cell.da = image * static_cast<Offset>(a.da_image * 4);
+            cell.ok = cell.ok && !map_unusable(a.hdr, min(image0 + image, a.N - 1), a.algo);
+        }
+        cell.from = cell.ok ? cell.from : Array::kNothing;
+        return cell;
+    };
+    const Cell first_cell = cell_of(lane);
+
 #pragma unroll 1
-    for (int chunk = wave; chunk < a.nchunks; chunk += nwaves) {
+    for (int chunk = first_chunk; chunk < a.nchunks; chunk += stride_chunk) {
         const int c0 = chunk * a.cc, nc = min(a.cc, a.C - c0);
-        // ---- the window: lane = cell of 64, all of a chunk's channels on the way together.  Cells without a
-        // source read zero (an offset past the end); channels past the last one hold anything ---------------
+        // ---- the window: lane = cell of 64, all of a chunk's channels on the way together.  Channels past the
+        // last one hold anything ---------------------------------------------------------------------------
         const Array buffer(source + c0 * channel_bytes, (a.N - image0) * image_bytes - c0 * channel_bytes);
+        Cell cell = first_cell;
 #pragma unroll 1
-        for (int i = lane; i < a.sets * kLanes; i += kLanes) {
-            int r, q;
-            if constexpr (kDense) { r = quotient(i, a.by_line); q = i - r * a.cols; }
-            else { q = quotient(i, a.by_line); r = i - q * a.rows; }
-            const int v = top + r, image = quotient(v, a.by_Ih), row = v - image * a.Ih, j = x0 * a.stride + q;
-            bool ok = i < a.cells && image0 + image < a.N && j < a.Iw;
-            Offset from;
-            if constexpr (kDense) {
-                const int hr = row - a.pad_h, jr = j - a.pad_w;
-                ok = ok && hr >= 0 && hr < a.H && jr >= 0 && jr < a.W;
-                from = (image * static_cast<Offset>(a.map_image) + static_cast<Offset>(hr) * a.map_r + static_cast<Offset>(jr) * a.map_x) * 4u;
-            } else {
-                from = ((static_cast<Offset>(image) * a.C * a.Iw + j) * a.bands + (row >> 6)) * sizeof(ColumnEntry);
-            }
-            from = ok ? from : Array::kNothing;
+        for (int i = lane;;) {
             float x[kChunk];
+            Offset at_channel = 0;
+            asm volatile("" : "+s"(at_channel));   // (added up as the loads go: sixteen multiples are not worth their registers)
             if constexpr (kDense) {
 #pragma unroll
-                for (int c = 0; c < kChunk; ++c) x[c] = buffer.load1(from, c * static_cast<Offset>(channel_bytes));
+                for (int c = 0; c < kChunk; ++c, at_channel += static_cast<Offset>(channel_bytes)) x[c] = buffer.load1(cell.from, at_channel);
                 if (a.relu) {   // the end of the layer that produced the map; cells outside the map stay zero
 #pragma unroll
                     for (int c = 0; c < kChunk; ++c) {
                         if (a.bias != nullptr) x[c] += a.bias[min(c0 + c, a.C - 1)];
-                        x[c] = ok && (__float_as_uint(x[c]) - 1u) < 0x7f800000u ? x[c] : 0.0f;
+                        x[c] = cell.ok && (__float_as_uint(x[c]) - 1u) < 0x7f800000u ? x[c] : 0.0f;
                     }
                 }
             } else {
-                const unsigned b = row & 63u, bit_lo = b < 32u ? 1u << b : 0u, bit_hi = b < 32u ? 0u : 1u << (b - 32u);
-                const unsigned below_lo = b < 32u ? bit_lo - 1u : ~0u, below_hi = b < 32u ? 0u : bit_hi - 1u;
-                uint4v e[kChunk];   // ColumnEntry: begin, count, rows_lo, rows_hi
+                uint3v e[kChunk];   // ColumnEntry: begin, rows_lo, rows_hi
 #pragma unroll
-                for (int c = 0; c < kChunk; ++c) e[c] = buffer.load4(from, c * static_cast<Offset>(channel_bytes));
-                ok = ok && !map_unusable(a.hdr, min(image0 + image, a.N - 1), a.algo);
+                for (int c = 0; c < kChunk; ++c, at_channel += static_cast<Offset>(channel_bytes)) e[c] = buffer.load3(cell.from, at_channel);
+                if (nc < kChunk) {   // channels past the last one: another image's entries, or the end of the table
+#pragma unroll
+                    for (int c = 0; c < kChunk; ++c) {
+                        e[c][1] = c < nc ? e[c][1] : 0u;
+                        e[c][2] = c < nc ? e[c][2] : 0u;
+                    }
+                }
+                // the cell's row among the column's rows, and those above it
+                const uint32_t bit = 1u << (cell.row & 31), bit_lo = cell.row < 32 ? bit : 0u, bit_hi = cell.row < 32 ? 0u : bit;
+                const uint32_t below_lo = cell.row < 32 ? bit - 1u : ~0u, below_hi = cell.row < 32 ? 0u : bit - 1u;
                 const Array runs(a.values + image0 * a.da_image, (a.N - image0) * a.da_image * 4);
-                const Offset da_bytes = image * static_cast<Offset>(a.da_image * 4);
 #pragma unroll
                 for (int c = 0; c < kChunk; ++c) {
-                    // (channels past the last one: another image's entries, or the end of the table)
-                    const bool has = ((e[c][2] & bit_lo) | (e[c][3] & bit_hi)) != 0u && ok && c < nc;
-                    const uint32_t where = e[c][0] + __popc(e[c][2] & below_lo) + __popc(e[c][3] & below_hi);
-                    x[c] = runs.load1(has ? where * Offset{4} + da_bytes : Array::kNothing, 0);
+                    const bool has = ((e[c][1] & bit_lo) | (e[c][2] & bit_hi)) != 0u;
+                    const uint32_t where = e[c][0] + __popc(e[c][1] & below_lo) + __popc(e[c][2] & below_hi);
+                    x[c] = runs.load1(has ? where * Offset{4} + cell.da : Array::kNothing, 0);
                 }
             }
-            if (i < a.cells) {
+            if (cell.inside) {
+                int to_channel = cell.to, cc = a.cc;
+                asm volatile("" : "+v"(to_channel), "+s"(cc));
 #pragma unroll
-                for (int c = 0; c < kChunk; ++c)
-                    if (c < a.cc) *reinterpret_cast<float *>(window + c * stride_c + (r * a.cols + q) * 4) = x[c];
+                for (int c = 0; c < kChunk; ++c, to_channel += stride_c)
+                    if (c < cc) *reinterpret_cast<float *>(window + to_channel) = x[c];
             }
+            i += kLanes;
+            if (i - lane >= a.sets * kLanes) break;
+            cell = cell_of(i);
         }
-        if (chunk == wave) __syncthreads();   // the table (every wavefront has a first chunk)
+        if (chunk == first_chunk) __syncthreads();   // the table (every wavefront has a first chunk)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -223,20 +266,25 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
         const int nq = nc * a.taps, steps = (nq + kStep - 1) / kStep;
         const uint32_t q0 = static_cast<uint32_t>(c0) * a.taps;
         const int4 *offsets = reinterpret_cast<const int4 *>(tab) + kk;
-        if (chunk != wave) {
+        if (chunk != first_chunk) {
 #pragma unroll
             for (int d = 0; d < D - 1; ++d) load(w[d], q0 + d * kStep);
         }
         int4 o = offsets[0];
-        auto step_of = [&](auto d_, int step) __attribute__((always_inline)) {
-            constexpr int d = decltype(d_)::value;
+        float x[D][4][T];   // the values of this step and, on their way, of the next
+        auto read = [&](float (&v)[4][T]) __attribute__((always_inline)) {
             const int off[4] = {o.x, o.y, o.z, o.w};
-            float x[4][T];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int t = 0; t < T; ++t) x[j][t] = *reinterpret_cast<const float *>(window + (base[t] + off[j]));
-            o = offsets[min(step + 1, steps - 1) * 4];
+                for (int t = 0; t < T; ++t) v[j][t] = *reinterpret_cast<const float *>(window + (base[t] + off[j]));
+        };
+        read(x[0]);
+        o = offsets[min(1, steps - 1) * 4];
+        auto step_of = [&](auto d_, int step) __attribute__((always_inline)) {
+            constexpr int d = decltype(d_)::value;
+            read(x[(d + 1) % D]);
+            o = offsets[min(step + 2, steps - 1) * 4];
             w[d].settle();
             load(w[(d + D - 1) % D], q0 + (step + D - 1) * kStep);
             if (step * kStep + kStep > nq) {   // indices past the chunk's last one: neither weight nor value counts
@@ -246,7 +294,7 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) w[d].w[mt][j] = ok ? w[d].w[mt][j] : 0.0f;
 #pragma unroll
-                    for (int t = 0; t < T; ++t) x[j][t] = ok ? x[j][t] : 0.0f;
+                    for (int t = 0; t < T; ++t) x[d][j][t] = ok ? x[d][j][t] : 0.0f;
                 }
             }
 #pragma unroll
@@ -255,7 +303,7 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
                 for (int t = 0; t < T; ++t)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt)
-                        acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[d].w[mt][j], x[j][t], acc[mt][t], 0, 0, 0);
+                        acc[mt][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[d].w[mt][j], x[d][j][t], acc[mt][t], 0, 0, 0);
         };
 #pragma unroll 1
         for (int step = 0; step < steps; step += D) {
@@ -271,7 +319,7 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
     // of kernels and position n of the tile of positions -----------------------------------------------
     constexpr int kRegs = MT * T * 4;
     float *red = reinterpret_cast<float *>(smem);
-    if (nwaves > 1) {
+    if (shared) {
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < T; ++t)
@@ -281,16 +329,15 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
                 for (int i = 0; i < 4; ++i) red[(wave * kRegs + (t * MT + mt) * 4 + i) * kLanes + lane] = acc[mt][t][i];
         __syncthreads();
     }
-    const int64_t plane = static_cast<int64_t>(a.Oh) * a.Ow;
+    const int left = a.K - kbase - 4 * kk * MT;   // kernels of the lane that exist
     auto store = [&](int reg, float s) __attribute__((always_inline)) {
-        const int t = reg / (4 * MT), mt = (reg / 4) % MT, i = reg % 4;
-        const int p = in_row0 + t * 16 + n, row = quotient(p, a.by_SW), image = quotient(y0 + row, a.by_Oh);
-        const int y = y0 + row - image * a.Oh, x = x0 + p - row * a.SW, k = kbase + (4 * kk + i) * MT + mt;
-        bool ok = p0 + t * 16 + n < positions && x < a.Ow && k < a.K;
-        if constexpr (!kDense) ok = ok && !map_unusable(a.hdr, min(image0 + image, a.N - 1), a.algo);
-        if (ok) a.out[(static_cast<int64_t>(image0 + image) * a.K + k) * plane + y * a.Ow + x] = s;
+        const int t = reg / (4 * MT), k = (reg % 4) * MT + (reg / 4) % MT;
+        int64_t at = to[0];
+#pragma unroll
+        for (int u = 1; u < T; ++u) at = t == u ? to[u] : at;
+        if (at >= 0 && k < left) a.out[at + k * plane] = s;
     };
-    if (nwaves > 1) {
+    if (shared) {
         for (int reg = wave; reg < kRegs; reg += nwaves) {
             float s = red[reg * kLanes + lane];
             for (int v = 1; v < nwaves; ++v) s += red[(v * kRegs + reg) * kLanes + lane];
@@ -310,6 +357,7 @@ __global__ __launch_bounds__(64 * max_waves(MT, T)) void conv_f32_kernel(const C
 
 struct ConvPlan {
     int mt, t, sw, cc, waves;
+    int whole;  // tiles that a wavefront takes alone (in: whether any may be); the others are shared by a workgroup
     bool far;   // a tile's share of an array spans 4 GiB or more: the kernel with 64-bit addresses
     int rows, cols, tiles, strips, mblocks, tab_bytes, window_bytes, lds;
     double cost;
@@ -340,33 +388,38 @@ bool evaluate(const Geometry &g, bool dense, ConvPlan *p)
     while (waves > 1 && p->tab_bytes + static_cast<int64_t>(waves) * p->window_bytes > kLdsLimit) --waves;
     const int rounds = (nchunks + waves - 1) / waves;
     p->waves = waves = (nchunks + rounds - 1) / rounds;
+    p->whole = waves == 1 ? static_cast<int>(std::min<int64_t>(blocks, INT32_MAX)) : (p->whole ? static_cast<int>(blocks / 1024 * 1024 / waves) * waves : 0);
     p->lds = std::max(p->tab_bytes + waves * p->window_bytes, waves > 1 ? waves * p->mt * p->t * 1024 : 0);
     if (p->lds > kLdsLimit || blocks >= (int64_t{1} << 31)) return false;
     // Estimated cycles.  Vector instructions do not overlap with fp32 matrix instructions on this part, so
     // what a wavefront spends per chunk adds up: matrix instructions (32 cycles each), the loads and
-    // additions around them, filling its window.  Then the load of the busiest compute unit, the latency of
-    // a lone wavefront, and the weights' way out of the L2.  The constants are fitted to 26 layers x every
-    // launch shape below, dense and columns, on MI355X.
-    const double step = p->mt * p->t * 128.0 + 22.0 + 43.0 * p->t + 7.0 * (dense ? p->mt : 2);
-    const double fill = sets * p->cc / 16.0;
-    const double store = p->mt * p->t * 55.0 * (waves > 1 ? 3.0 : 1.0);
-    const double wave = rounds * (steps * step + fill * (dense ? 1240.0 : 2000.0) + 330.0) + 1500.0 + store;
-    const double per_unit = blocks / static_cast<double>(kComputeUnits);
-    const double busiest = per_unit <= 8.0 ? std::ceil(per_unit) : per_unit + 0.2;
-    double waves_per_simd = busiest * waves / 4.0;
-    if (waves < 4)
-        waves_per_simd = blocks * waves < 16 * kComputeUnits ? std::ceil(blocks * waves / (4.0 * kComputeUnits)) : (per_unit + 0.2) * waves / 4.0;
-    const int simd_waves = !dense ? 4 : (p->mt * p->t >= 8 ? 5 : (p->mt * p->t >= 4 ? 6 : 7));
-    const int resident = std::max(1, std::min(4 * simd_waves / waves, kLdsLimit / p->lds));
-    const double active = std::min(resident * waves / 4.0, std::max(waves_per_simd, 1.0));
-    const double through = waves_per_simd * wave * (1.0 + 0.6 / active);
-    const double alone = rounds * (steps * (step + 416.0) + sets * (dense ? 5630.0 : 4510.0)) + 9830.0;
-    const double weights = per_unit * 16.0 * p->mt * g.C * taps * 4.0 / 150.0 * (dense ? 1.6 : 1.0);
+    // additions around them, filling its window.  Then the load of the busiest SIMD - whole tiles first, then
+    // the shared ones -, the latency of a lone wavefront, and the weights' way out of the L2.  The constants
+    // are fitted to 37 layers of 1 to 32 images x every launch shape below, dense and columns, on MI355X: the
+    // shape picked is 3 % slower than the best one on average.
+    const double step = p->mt * p->t * 128.0 + 6.6 + 47.9 * p->t + 0.9 * p->mt;
+    const double chunk = steps * step + sets * p->cc / 16.0 * (dense ? 1720.0 : 1070.0) + 625.0;
+    const double store = p->mt * p->t * 175.0;
+    const double alone_in_tile = nchunks * chunk + 1500.0 + store, sharing = rounds * chunk + 1500.0 + 3.0 * store;
+    double whole = p->whole / 1024.0;   // per SIMD
+    if (waves == 1) whole = whole <= 5.0 ? std::ceil(whole) : whole + 0.32;
+    const int64_t rest = blocks - p->whole;
+    const double per_unit = rest / static_cast<double>(kComputeUnits);
+    double shared = (per_unit <= 8.0 ? std::ceil(per_unit) : per_unit + 0.16) * waves / 4.0;
+    if (waves < 4 && rest > 0) shared = rest * waves < 4096 ? std::ceil(rest * waves / 1024.0) : (per_unit + 0.16) * waves / 4.0;
+    const int resident = std::max(1, std::min(4 * (p->mt * p->t >= 8 ? 4 : 5) / waves, kLdsLimit / p->lds));
+    const double active = std::min(resident * waves / 4.0, std::max(whole + shared, 1.0));
+    const double through = (whole * alone_in_tile + shared * sharing) * (1.0 + 0.47 / active);
+    const double alone = (p->whole > 0 ? nchunks : rounds) * (steps * (step + 582.0) + sets * (dense ? 5840.0 : 3760.0)) + 11300.0;
+    const double weights = blocks / static_cast<double>(kComputeUnits) * 16.0 * p->mt * g.C * taps * 4.0 / 146.0 * (dense ? 1.6 : 1.0);
     p->cost = std::max(through, alone) + weights;
     return true;
 }
 
-// The launch shape with the smallest estimate: kernels and positions of a wavefront, strips as wide as a
+// The launch shape with the smallest estimate.  A tile belongs to a wavefront alone where there are enough of them
+// (no additions at the end), rounded down to a multiple of the 1024 SIMDs; the tiles left over - and all
+// of them in small launches - are shared by the wavefronts of a workgroup, so that the last round is a short
+// one (128@56, 32 images: 285 -> 270 us, 5x5 64@27: 146 -> 131).  Kernels and positions of a wavefront, strips as wide as a
 // small map or eight or four columns (compact windows), chunks of sixteen channels (whole steps whatever
 // the kernel), fewer for layers of few channels or where a window of sixteen does not fit.
 ConvPlan conv_plan(const Geometry &g, bool dense)
@@ -383,15 +436,18 @@ ConvPlan conv_plan(const Geometry &g, bool dense)
                     if (sw > g.Ow || (sw > 20 && g.Ow >= 8)) continue;
                     for (int waves : {1, 2, 4, 8, 16}) {
                         if (waves > 1 && waves / 2 * cc >= g.C) break;
-                        ConvPlan p;
-                        p.mt = mt; p.t = t; p.sw = sw; p.cc = std::min(cc, g.C); p.waves = waves;
-                        if (evaluate(g, dense, &p) && (best.cost < 0.0 || p.cost < best.cost)) best = p;
+                        for (int whole : {0, 1}) {
+                            ConvPlan p;
+                            p.mt = mt; p.t = t; p.sw = sw; p.cc = std::min(cc, g.C); p.waves = waves; p.whole = whole;
+                            if (evaluate(g, dense, &p) && (best.cost < 0.0 || p.cost < best.cost)) best = p;
+                        }
                     }
                 }
         }
     }
     if (best.cost < 0.0) {   // large strides: the least window there is
         best.mt = best.t = best.sw = best.cc = best.waves = 1;
+        best.whole = 0;
         if (!evaluate(g, dense, &best)) best.cost = -1.0;
     }
     return best;
@@ -411,7 +467,7 @@ template <bool kDense>
 int launch(const ConvPlan &p, const ConvArgs &a, const char *name, hipStream_t stream)
 {
     KernelTimer timer(name, stream);
-    const dim3 grid(p.tiles * p.strips * p.mblocks), block(p.waves * kLanes);
+    const dim3 grid(p.tiles * p.strips * p.mblocks - p.whole + p.whole / p.waves), block(p.waves * kLanes);
     if (p.far) hipLaunchKernelGGL((conv_f32_kernel<1, 1, kDense, true>), grid, block, p.lds, stream, a);
 #define CPOCONV_CASE(MT, T) \
     else if (p.mt == MT && p.t == T) hipLaunchKernelGGL((conv_f32_kernel<MT, T, kDense, false>), grid, block, p.lds, stream, a);
@@ -431,6 +487,7 @@ ConvArgs make_args(const Geometry &g, const ConvPlan &p, bool dense)
     a.sets = (a.cells + kLanes - 1) / kLanes;
     a.cc = p.cc; a.nchunks = (g.C + p.cc - 1) / p.cc;
     a.tiles = p.tiles; a.per_m = p.tiles * p.strips;
+    a.whole_blocks = p.whole / p.waves;
     a.tab_bytes = p.tab_bytes; a.window_bytes = p.window_bytes;
     a.by_SW = divisor(p.sw); a.by_Oh = divisor(g.Oh); a.by_Ih = divisor(g.Ih); a.by_line = divisor(dense ? p.cols : p.rows);
     a.by_taps = divisor(a.taps); a.by_kw = divisor(g.kw); a.by_tiles = divisor(p.tiles); a.by_per_m = divisor(a.per_m);

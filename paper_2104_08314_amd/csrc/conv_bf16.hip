@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * max_waves(TM, TN)) void conv_bf16_kernel(const
     const int group = wave / team, in_group = wave - group * team, wn = in_group / a.wm, wm = in_group - wn * a.wm;
     const int thread = in_group * kLanes + lane, threads = team * kLanes;
 
-    const int number = tile_number();
+    const int number = dealt(blockIdx.x, gridDim.x);
     const int mb = quotient(number, a.by_per_m), in_m = number - mb * a.per_m;
     const int strip = quotient(in_m, a.by_tiles), tile = in_m - strip * a.tiles;
     const int kbase = (mb * a.wm + wm) * 32 * TM, p0 = tile * 32 * TN * a.wn, x0 = strip * a.SW;

@@ -24,6 +24,7 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kLanes - 1); }
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint3v __attribute__((ext_vector_type(3)));
 typedef uint32_t uint2v __attribute__((ext_vector_type(2)));
 
 // Loads through a buffer descriptor: a 32-bit offset per lane and one per wavefront, no address
@@ -45,6 +46,10 @@ struct Buffer {
     __device__ __forceinline__ uint4v load4(Offset lane_offset, Offset offset) const
     {
         return __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_offset, offset, 0);
+    }
+    __device__ __forceinline__ uint3v load3(Offset lane_offset, Offset offset) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b96(rsrc, lane_offset, offset, 0);
     }
     template <int N> __device__ __forceinline__ void load(float *f, Offset lane_offset, Offset offset) const
     {
@@ -85,6 +90,13 @@ struct Buffer<true> {
         for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(load1(lane_offset, offset + 4 * i));
         return v;
     }
+    __device__ __forceinline__ uint3v load3(Offset lane_offset, Offset offset) const
+    {
+        uint3v v;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = __float_as_uint(load1(lane_offset, offset + 4 * i));
+        return v;
+    }
     template <int N> __device__ __forceinline__ void load(float *f, Offset lane_offset, Offset offset) const
     {
 #pragma unroll
@@ -92,13 +104,13 @@ struct Buffer<true> {
     }
 };
 
-// Tile of this workgroup.  Workgroups go to the XCDs in turn: the tile numbers (kernel block outermost)
-// are dealt so that an XCD holds a contiguous range of them - its L2 then fetches one stretch of the map
-// and, with eight kernel blocks or more, its share of the weights only.
-__device__ __forceinline__ int tile_number()
+// Tile of the i-th of `total` workgroups.  Workgroups go to the XCDs in turn: the tile numbers (kernel block
+// outermost) are dealt so that an XCD holds a contiguous range of them - its L2 then fetches one stretch of
+// the map and, with eight kernel blocks or more, its share of the weights only.
+__device__ __forceinline__ int dealt(int i, int total)
 {
-    const int issued = blockIdx.x, total = gridDim.x, xcd = issued % kXcds;
-    return xcd * (total / kXcds) + min(xcd, total % kXcds) + issued / kXcds;
+    const int xcd = i % kXcds;
+    return xcd * (total / kXcds) + min(xcd, total % kXcds) + i / kXcds;
 }
 
 constexpr int kComputeUnits = 256;

@@ -460,13 +460,13 @@ __global__ __launch_bounds__(kEncThreads) void encode_kernel(const Geometry g, c
                 if (w >= row_bands) continue;
                 const int n = __popcll(m[w]);
                 table[column_j(g, vi) * row_bands + w] =
-                    ColumnEntry{at, n, static_cast<uint32_t>(m[w]), static_cast<uint32_t>(m[w] >> 32)};
+                    ColumnEntry{at, static_cast<uint32_t>(m[w]), static_cast<uint32_t>(m[w] >> 32)};
                 at += n;
             }
         }
         if (b == 0)
             for (int i = lane; i < g.Iw * row_bands; i += kLanes)
-                if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0, 0u, 0u};
+                if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0u, 0u};
     }
 
     // ---- ptr of the band's types ------------------------------------------------------------------------
@@ -685,7 +685,6 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
                                                                                       : __popcll(mask));
             if (table != nullptr) {   // the entry's rows now, its place in DA when that is known
                 ColumnEntry *e = table + column_j(g, tid) * row_bands + q;
-                e->count = __popcll(mask);
                 e->rows_lo = static_cast<uint32_t>(mask);
                 e->rows_hi = static_cast<uint32_t>(mask >> 32);
             }
@@ -799,7 +798,7 @@ __global__ __launch_bounds__(kThreads) void encode_channel_kernel(const Geometry
         if (tid < g.n_cols)
             for (int q = 0; q < nchunks; ++q) table[column_j(g, tid) * row_bands + q].begin = da_off + col_excl[tid] + cnt_q[q][tid];
         for (int i = tid; i < g.Iw * row_bands; i += kThreads)
-            if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0, 0u, 0u};
+            if (!encoded_column(g, i / row_bands)) table[i] = ColumnEntry{0, 0u, 0u};
     }
 
     // ---- ptr of this channel -------------------------------------------------------------
@@ -1125,8 +1124,8 @@ __global__ __launch_bounds__(NW *kLanes, 8) void encode_channel64_kernel(const G
     if (columns_all != nullptr && wave == NW - 1) {
         ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
         if (col_ok)
-            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
-        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
+            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
+        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0u, 0u};
     }
 
     if (nnz_c == 0) {
@@ -1381,8 +1380,8 @@ __global__ __launch_bounds__(kThreads) void encode_small_kernel(const Geometry g
     if (columns_all != nullptr) {
         ColumnEntry *row = columns_all + (static_cast<int64_t>(image) * g.C + c) * g.Iw;
         if (col_ok)
-            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, cnt, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
-        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0, 0u, 0u};
+            row[my_jr + g.pad_w] = ColumnEntry{da_off + excl, static_cast<uint32_t>(colmask), static_cast<uint32_t>(colmask >> 32)};
+        if (lane < g.Iw && !encoded_column(g, lane)) row[lane] = ColumnEntry{0, 0u, 0u};
     }
 
     // ---- ptr ----------------------------------------------------------------------------------------
